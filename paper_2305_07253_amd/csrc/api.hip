@@ -10,6 +10,7 @@
 
 #include "api_internal.hpp"
 #include "bvh_build.hpp"
+#include "entry.hpp"
 
 static_assert(hyb::kStackDepth >= hyb::kStackDepth4, "trace stack smaller than the builder's bound");
 
@@ -33,7 +34,7 @@ hyb_status hyb_build_bvh(const float* verts, int64_t n_verts, const int32_t* tri
     if (!out) return HYB_ERR_INVALID_ARG;
     *out = nullptr;
     hyb::BvhHost host;
-    int rc = hyb::build_bvh_host(verts, n_verts, tris, n_tris, &host);
+    int rc = hyb::build_bvh_host(verts, n_verts, tris, n_tris, &host, false);
     if (rc == 1) return HYB_ERR_INVALID_ARG;
     if (rc != 0) return HYB_ERR_UNSUPPORTED;
     hyb_bvh_s* b = new (std::nothrow) hyb_bvh_s;
@@ -46,26 +47,33 @@ hyb_status hyb_build_bvh(const float* verts, int64_t n_verts, const int32_t* tri
     for (int a = 0; a < 3; ++a) {
         b->lo[a] = host.lo[a];
         b->hi[a] = host.hi[a];
+        b->grid.lo[a] = host.entry_lo[a];
     }
+    b->grid.size = host.entry_size;
+    b->grid.res = host.entry_res;
+    b->grid.levels = host.entry_levels;
     const size_t node_bytes = host.nodes.size() * sizeof(float);
-    const size_t tri_bytes = std::max<size_t>(host.tris.size(), 12) * sizeof(float);
     const size_t node4_bytes = host.nodes4.size() * sizeof(float);
-    const size_t entry_bytes = host.entry.size() * sizeof(int32_t);
-    b->entry_res = host.entry_res;
-    b->entry_levels = host.entry_levels;
-    b->entry_size = host.entry_size;
-    for (int a = 0; a < 3; ++a) b->entry_lo[a] = host.entry_lo[a];
-    if (e == hipSuccess && entry_bytes) e = hipMalloc(&b->entry, entry_bytes);
-    if (e == hipSuccess && entry_bytes)
-        e = hipMemcpyAsync(b->entry, host.entry.data(), entry_bytes, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipMalloc(&b->nodes, node_bytes);
-    if (e == hipSuccess) e = hipMalloc(&b->nodes4, node4_bytes);
-    if (e == hipSuccess) e = hipMalloc(&b->tris, tri_bytes);
-    if (e == hipSuccess) e = hipMemcpyAsync(b->nodes, host.nodes.data(), node_bytes, hipMemcpyHostToDevice, st);
+    const size_t tri_bytes = host.tris.size() * sizeof(float);
+    const size_t entry_bytes = host.entry_res ? hyb::entry_total(host.entry_res) * sizeof(int32_t) : 0;
+    // one allocation: an allocation and its release cost host time each
+    const auto up = [](size_t bytes) { return (bytes + 255) & ~size_t(255); };
+    const size_t total = up(node_bytes) + up(node4_bytes) + up(std::max<size_t>(tri_bytes, 48)) + entry_bytes;
+    if (e == hipSuccess) e = hipMalloc(&b->memory, total);
+    if (e == hipSuccess) {
+        char* p = static_cast<char*>(b->memory);
+        b->nodes4 = reinterpret_cast<float4*>(p);
+        b->nodes = reinterpret_cast<float4*>(p += up(node4_bytes));
+        b->tris = reinterpret_cast<float4*>(p += up(node_bytes));
+        b->entry = reinterpret_cast<int32_t*>(p += up(std::max<size_t>(tri_bytes, 48)));
+        e = hipMemcpyAsync(b->nodes, host.nodes.data(), node_bytes, hipMemcpyHostToDevice, st);
+    }
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->nodes4, host.nodes4.data(), node4_bytes, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess && !host.tris.empty())
-        e = hipMemcpyAsync(b->tris, host.tris.data(), host.tris.size() * sizeof(float), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess && tri_bytes)
+        e = hipMemcpyAsync(b->tris, host.tris.data(), tri_bytes, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess && entry_bytes)
+        e = hyb::launch_entries(b->nodes4, b->tris, b->n_nodes, b->grid, b->entry, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         hyb_bvh_destroy(b);
@@ -85,10 +93,7 @@ hyb_status hyb_bvh_info(hyb_bvh bvh, int64_t* n_nodes, int64_t* n_tris, int32_t*
 
 hyb_status hyb_bvh_destroy(hyb_bvh bvh) {
     if (!bvh) return HYB_ERR_INVALID_ARG;
-    if (bvh->nodes) (void)hipFree(bvh->nodes);
-    if (bvh->nodes4) (void)hipFree(bvh->nodes4);
-    if (bvh->entry) (void)hipFree(bvh->entry);
-    if (bvh->tris) (void)hipFree(bvh->tris);
+    if (bvh->memory) (void)hipFree(bvh->memory);
     delete bvh;
     return HYB_OK;
 }

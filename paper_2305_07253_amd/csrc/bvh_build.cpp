@@ -11,6 +11,8 @@
 #include <cstring>
 #include <limits>
 
+#include "entry.hpp"
+
 namespace hyb {
 namespace {
 
@@ -166,79 +168,44 @@ inline float bits_as_float(int32_t v) {
 
 constexpr int kEntryRes = 64;
 
-// Entry points of BvhHost (see the header): the finest level by a box query
-// per voxel, the coarser ones as the common ancestor of their 8 children.
-void build_entries(BvhHost* out) {
+// Placement of the entry pyramid over the mesh bounds.
+void place_entries(BvhHost* out) {
     out->entry.clear();
     out->entry_res = 0;
     out->entry_levels = 0;
-    const size_t n4 = out->nodes4.size() / 32;
     float ext = 0.0f;
     for (int a = 0; a < 3; ++a) ext = std::max(ext, out->hi[a] - out->lo[a]);
-    if (n4 == 0 || !(ext > 0.0f)) return;
-    const float* nd = out->nodes4.data();
-    auto ref_of = [&](size_t node, int c) {
-        int32_t r;
-        std::memcpy(&r, nd + 32 * node + 24 + c, 4);
-        return r;
-    };
-    // parents and depths of nodes and leaves
-    // a leaf is identified by its first triangle, (~ref) >> 3
-    std::vector<int32_t> parent(n4, -1), depth(n4, 0), leaf_parent(out->tris.size() / 12 + 1, -1);
-    for (size_t i = 0; i < n4; ++i)  // children come after their parent in the array
-        for (int c = 0; c < 4; ++c) {
-            const int32_t r = ref_of(i, c);
-            if (r == kEmptyRef) continue;
-            if (r >= 0) {
-                parent[r] = static_cast<int32_t>(i);
-                depth[r] = depth[i] + 1;
-            } else {
-                leaf_parent[(~r) >> 3] = static_cast<int32_t>(i);
-            }
-        }
-    auto depth_of = [&](int32_t r) { return r >= 0 ? depth[r] : depth[leaf_parent[(~r) >> 3]] + 1; };
-    auto up = [&](int32_t r) { return r >= 0 ? parent[r] : leaf_parent[(~r) >> 3]; };
-    auto lca = [&](int32_t a, int32_t b) {
-        if (a == kEmptyRef) return b;
-        if (b == kEmptyRef) return a;
-        int da = depth_of(a), db = depth_of(b);
-        while (da > db) { a = up(a); --da; }
-        while (db > da) { b = up(b); --db; }
-        while (a != b) { a = up(a); b = up(b); }
-        return a;
-    };
-
+    if (out->nodes4.empty() || !(ext > 0.0f)) return;
     const int E = kEntryRes;
     const float size = ext / static_cast<float>(E) * (1.0f + 1e-4f);
     for (int a = 0; a < 3; ++a) out->entry_lo[a] = out->lo[a] - 0.5f * (size * E - (out->hi[a] - out->lo[a]));
+    // bounds too far apart for FP32: no pyramid, traversals start at the root
+    if (!std::isfinite(size) || !std::isfinite(out->entry_lo[0] + out->entry_lo[1] + out->entry_lo[2])) return;
     out->entry_size = size;
-    int levels = 0;
-    size_t total = 0;
-    for (int e = E; e >= 1; e >>= 1) {
-        const size_t w = static_cast<size_t>(2 * e - 1);
-        total += w * w * w;
-        ++levels;
-    }
-    out->entry.assign(total, kEmptyRef);
-    // every leaf joins each finest half-cell its box overlaps, the box grown
-    // by a margin (FP32 rounding of segment end points is far below it)
-    int H = 2 * E;
-    const double half = 0.5 * static_cast<double>(size);
+    out->entry_res = E;
+    for (int e = E; e >= 1; e >>= 1) ++out->entry_levels;
+}
+
+// Entry points of BvhHost (see the header): the finest level by a box query
+// per voxel, the coarser ones as the common ancestor of their 8 children.
+void build_entries(BvhHost* out) {
+    if (out->entry_res == 0) return;
+    const size_t n4 = out->nodes4.size() / 32;
+    const float* nd = out->nodes4.data();
+    auto lca = [&](int32_t a, int32_t b) { return entry_lca(nd, out->tris.data(), a, b); };
+    out->entry.assign(static_cast<size_t>(entry_total(out->entry_res)), kEmptyRef);
+    // every leaf joins each finest half-cell its box overlaps
+    int H = 2 * out->entry_res;
     std::vector<int32_t> cells(static_cast<size_t>(H) * H * H, kEmptyRef);
-    const double margin = 1e-3 * size;
     for (size_t i = 0; i < n4; ++i)
         for (int c = 0; c < 4; ++c) {
-            const int32_t r = ref_of(i, c);
-            if (r == kEmptyRef || r >= 0) continue;
             const float* q = nd + 32 * i;
+            const int32_t r = entry_word(q + 24 + c);
+            if (r == kEmptyRef || r >= 0) continue;
             int v0[3], v1[3];
-            for (int a = 0; a < 3; ++a) {
-                const double qlo = q[8 * a + c], qhi = q[8 * a + 4 + c];
-                const double slack = margin + 1e-6 * (1.0 + std::max(std::fabs(qlo), std::fabs(qhi)));
-                const double u0 = (qlo - slack - out->entry_lo[a]) / half, u1 = (qhi + slack - out->entry_lo[a]) / half;
-                v0[a] = static_cast<int>(std::floor(std::min(std::max(u0, 0.0), H - 1.0)));
-                v1[a] = static_cast<int>(std::floor(std::min(std::max(u1, 0.0), H - 1.0)));
-            }
+            for (int a = 0; a < 3; ++a)
+                entry_range(q[8 * a + c], q[8 * a + 4 + c], out->entry_lo[a], out->entry_size, out->entry_res, v0[a],
+                            v1[a]);
             for (int z = v0[2]; z <= v1[2]; ++z)
                 for (int y = v0[1]; y <= v1[1]; ++y)
                     for (int x = v0[0]; x <= v1[0]; ++x) {
@@ -247,7 +214,7 @@ void build_entries(BvhHost* out) {
                     }
         }
     size_t off = 0;
-    for (int l = 0; l < levels; ++l) {
+    for (int l = 0; l < out->entry_levels; ++l) {
         // windows of 2 x 2 x 2 half-cells of this level
         const int W = H - 1;
         for (int z = 0; z < W; ++z)
@@ -261,7 +228,7 @@ void build_entries(BvhHost* out) {
                     out->entry[off + x + static_cast<size_t>(W) * (y + static_cast<size_t>(W) * z)] = acc;
                 }
         off += static_cast<size_t>(W) * W * W;
-        if (l + 1 == levels) break;
+        if (l + 1 == out->entry_levels) break;
         // the next level's half-cells: 2 x 2 x 2 of this level's
         const int h = H / 2;
         std::vector<int32_t> up(static_cast<size_t>(h) * h * h, kEmptyRef);
@@ -278,13 +245,12 @@ void build_entries(BvhHost* out) {
         cells.swap(up);
         H = h;
     }
-    out->entry_res = E;
-    out->entry_levels = levels;
 }
 
 }  // namespace
 
-int build_bvh_host(const float* verts, int64_t n_verts, const int32_t* tris, int64_t n_tris, BvhHost* out) {
+int build_bvh_host(const float* verts, int64_t n_verts, const int32_t* tris, int64_t n_tris, BvhHost* out,
+                   bool entries) {
     if (n_verts < 0 || n_tris < 0 || (n_verts > 0 && !verts) || (n_tris > 0 && !tris) || !out) return 1;
     if (n_tris > (int64_t(1) << 28)) return 4;
     for (int64_t i = 0; i < 3 * n_verts; ++i)
@@ -391,6 +357,8 @@ int build_bvh_host(const float* verts, int64_t n_verts, const int32_t* tris, int
             write4(s, &kid, root < 0 ? 0 : 1);
             float* q = out->nodes4.data() + 32 * static_cast<size_t>(s);
             for (int c = 0; c < 4; ++c) q[24 + c] = bits_as_float(c == 0 && root >= 0 ? leaf_of(root) : kEmptyRef);
+            q[kNode4Parent] = bits_as_float(-1);
+            if (root >= 0) out->tris[kTriLeafParent] = bits_as_float(0);
             return;
         }
         // `pushed`: stack entries a traversal can hold on arrival at the node
@@ -399,6 +367,7 @@ int build_bvh_host(const float* verts, int64_t n_verts, const int32_t* tris, int
         struct Item { int tn; int32_t slot; int depth; int pushed; };
         std::vector<Item> st;
         st.push_back({root, alloc4(), 1, 0});
+        out->nodes4[kNode4Parent] = bits_as_float(-1);
         while (!st.empty()) {
             const Item it = st.back();
             st.pop_back();
@@ -428,8 +397,12 @@ int build_bvh_host(const float* verts, int64_t n_verts, const int32_t* tris, int
             for (int c = 0; c < nk; ++c) {
                 if (b.nodes[kids[c]].count > 0) {
                     refs[c] = leaf_of(kids[c]);
+                    out->tris[12 * static_cast<size_t>((~refs[c]) >> 3) + kTriLeafParent] = bits_as_float(it.slot);
                 } else {
                     refs[c] = alloc4();
+                    float* child = out->nodes4.data() + 32 * static_cast<size_t>(refs[c]);
+                    child[kNode4Parent] = bits_as_float(it.slot);
+                    child[kNode4Depth] = bits_as_float(it.depth);
                     pending[np++] = {kids[c], refs[c], it.depth + 1, it.pushed + nk - 1};
                 }
             }
@@ -444,7 +417,8 @@ int build_bvh_host(const float* verts, int64_t n_verts, const int32_t* tris, int
         write_children(s, empty_box, kEmptyRef, empty_box, kEmptyRef);
         out->depth = 1;
         emit4();
-        build_entries(out);
+        place_entries(out);
+        if (entries) build_entries(out);
         return 0;
     }
     if (b.nodes[root].count > 0) {
@@ -453,7 +427,8 @@ int build_bvh_host(const float* verts, int64_t n_verts, const int32_t* tris, int
         write_children(s, b.nodes[root].box, lr, empty_box, kEmptyRef);
         out->depth = 1;
         emit4();
-        build_entries(out);
+        place_entries(out);
+        if (entries) build_entries(out);
         return 0;
     }
     // iterative pre-order so the left child usually follows its parent in memory
@@ -481,7 +456,8 @@ int build_bvh_host(const float* verts, int64_t n_verts, const int32_t* tris, int
     out->depth = b.max_depth;
     emit4();
     if (out->stack4 > kStackDepth4) return 4;
-    build_entries(out);
+    place_entries(out);
+    if (entries) build_entries(out);
     return 0;
 }
 

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bvh_build.hpp"
+
 namespace hyb {
 
 enum TraceMode : int { kCombined = 0, kBvhOnly = 1, kDfOnly = 2, kShadow = 3 };
@@ -90,6 +92,11 @@ hipError_t launch_quantize(int fmt, float* values, int32_t n, void* out, float* 
 size_t df_backward_workspace(int64_t n, int32_t n_grid);
 hipError_t launch_df_backward(const TraceArgs& a, const float* t_hit, const float* grad_t, float* grad_grid,
                               void* workspace, size_t workspace_bytes, hipStream_t stream);
+
+// The traversal entry pyramid of a tree (BvhHost::entry) into `entry`
+// (entry_total(g.res) words).
+hipError_t launch_entries(const float4* nodes4, const float4* tris, int64_t n_nodes, const EntryGrid& g,
+                          int32_t* entry, hipStream_t stream);
 
 struct SdfBuildArgs {
     const float4* nodes;
