@@ -52,26 +52,24 @@ hyb_status hyb_build_bvh(const float* verts, int64_t n_verts, const int32_t* tri
     b->grid.size = host.entry_size;
     b->grid.res = host.entry_res;
     b->grid.levels = host.entry_levels;
-    const size_t node_bytes = host.nodes.size() * sizeof(float);
+    host.tris.resize(host.tris.size() + 4, 0.0f);  // the boundary sum's zero travels with the triangles
     const size_t node4_bytes = host.nodes4.size() * sizeof(float);
     const size_t tri_bytes = host.tris.size() * sizeof(float);
     const size_t entry_bytes = host.entry_res ? hyb::entry_total(host.entry_res) * sizeof(int32_t) : 0;
     // one allocation: an allocation and its release cost host time each
     const auto up = [](size_t bytes) { return (bytes + 255) & ~size_t(255); };
-    const size_t total = up(node_bytes) + up(node4_bytes) + up(std::max<size_t>(tri_bytes, 48)) + entry_bytes;
+    const size_t total = up(node4_bytes) + up(std::max<size_t>(tri_bytes, 64)) + entry_bytes;
     if (e == hipSuccess) e = hipMalloc(&b->memory, total);
     if (e == hipSuccess) {
         char* p = static_cast<char*>(b->memory);
         b->nodes4 = reinterpret_cast<float4*>(p);
-        b->nodes = reinterpret_cast<float4*>(p += up(node4_bytes));
-        b->tris = reinterpret_cast<float4*>(p += up(node_bytes));
-        b->entry = reinterpret_cast<int32_t*>(p += up(std::max<size_t>(tri_bytes, 48)));
-        e = hipMemcpyAsync(b->nodes, host.nodes.data(), node_bytes, hipMemcpyHostToDevice, st);
-    }
-    if (e == hipSuccess)
+        b->tris = reinterpret_cast<float4*>(p += up(node4_bytes));
+        b->boundary = reinterpret_cast<unsigned long long*>(p + tri_bytes - 16);
+        b->entry = reinterpret_cast<int32_t*>(p + up(std::max<size_t>(tri_bytes, 64)));
         e = hipMemcpyAsync(b->nodes4, host.nodes4.data(), node4_bytes, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess && tri_bytes)
-        e = hipMemcpyAsync(b->tris, host.tris.data(), tri_bytes, hipMemcpyHostToDevice, st);
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(b->tris, host.tris.data(), tri_bytes, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hyb::launch_mesh_boundary(b->tris, n_tris, b->boundary, st);
     if (e == hipSuccess && entry_bytes)
         e = hyb::launch_entries(b->nodes4, b->tris, b->n_nodes, b->grid, b->entry, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -123,11 +121,14 @@ hyb_status hyb_build_sdf(hyb_bvh bvh, int32_t n, const float* grid4, uint32_t fl
     std::memcpy(s->grid4, g4, sizeof(g4));
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t bytes = sizeof(float) * static_cast<size_t>(n) * n * n;
-    hipError_t e = hipMalloc(&s->values, bytes);
-    if (e == hipSuccess) {
-        hyb::SdfBuildArgs a;
-        a.nodes = bvh->nodes;
+    size_t store_bytes = 0;
+    hyb_status rc = from_hip(hipMalloc(&s->values, bytes));
+    if (rc == HYB_OK) rc = allocate_store(s, &store_bytes);
+    if (rc == HYB_OK) {
+        hyb::SdfBuildArgs a = {};
+        a.nodes4 = bvh->nodes4;
         a.tris = bvh->tris;
+        a.boundary = bvh->boundary;
         a.n_grid = n;
         a.lo_x = g4[0];
         a.lo_y = g4[1];
@@ -135,9 +136,9 @@ hyb_status hyb_build_sdf(hyb_bvh bvh, int32_t n, const float* grid4, uint32_t fl
         a.h = g4[3];
         a.exterior_solid = (flags & HYB_SDF_EXTERIOR_SOLID) ? 1 : 0;
         a.out = s->values;
-        e = hyb::launch_sdf_build(a, st);
+        // the kernels' copy is written last: until then it is the build's scratch
+        rc = from_hip(hyb::launch_sdf_build(a, s->store, store_bytes, st));
     }
-    hyb_status rc = from_hip(e);
     if (rc == HYB_OK) rc = quantize(s, st);
     if (rc == HYB_OK) rc = from_hip(hipMalloc(&s->dev_bounds, sizeof(float) * hyb::kDeviceBounds));
     if (rc == HYB_OK) rc = compute_lipschitz(s, st);
@@ -167,6 +168,8 @@ hyb_status hyb_sdf_from_grid(const float* values, int32_t n, const float* grid4,
     if (e == hipSuccess) e = hipMalloc(&s->values, bytes);
     if (e == hipSuccess) e = hipMemcpyAsync(s->values, values, bytes, hipMemcpyDeviceToDevice, st);
     hyb_status rc = from_hip(e);
+    size_t store_bytes = 0;
+    if (rc == HYB_OK) rc = allocate_store(s, &store_bytes);
     // the compact formats would turn a NaN input into a finite code
     if (rc == HYB_OK && fmt != HYB_SDF_F32) rc = check_finite(s, st);
     if (rc == HYB_OK) rc = quantize(s, st);

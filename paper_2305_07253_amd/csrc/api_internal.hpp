@@ -15,9 +15,9 @@
 
 struct hyb_bvh_s {
     int device = 0;
-    void* memory = nullptr;    // one allocation, which the four arrays below share
-    float4* nodes = nullptr;   // binary tree (64-byte nodes): the distance-field build's queries
-    float4* nodes4 = nullptr;  // the same tree with four children per node (128 bytes): the trace kernels
+    void* memory = nullptr;    // one allocation, which the arrays below share
+    float4* nodes4 = nullptr;  // four children per node (128 bytes)
+    unsigned long long* boundary = nullptr;  // launch_mesh_boundary's sum
     int32_t* entry = nullptr;  // traversal entry pyramid (BvhHost::entry)
     hyb::EntryGrid grid;       // the pyramid's placement
     float4* tris = nullptr;
@@ -142,19 +142,25 @@ inline hyb_status deferred_bounds(hyb_sdf_s* s, hipStream_t stream) {
     return HYB_OK;
 }
 
-// Writes the kernels' copy of the FP32 samples in s->values (storage format,
-// bricked layout); for the compact formats the dequantized values replace
-// s->values in place.
-inline hyb_status quantize(hyb_sdf_s* s, hipStream_t stream) {
+// Allocates the kernels' copy of the samples; *bytes receives its size.
+inline hyb_status allocate_store(hyb_sdf_s* s, size_t* bytes) {
     const int fmt = s->fmt == HYB_SDF_F32 ? hyb::kF32 : (s->fmt == HYB_SDF_F16 ? hyb::f16_layout(s->n) : hyb::kI8);
     s->layout = fmt;
     const size_t count = static_cast<size_t>(hyb::brick_storage(fmt, s->n));
     const size_t elem = s->fmt == HYB_SDF_F32 ? 4 : (s->fmt == HYB_SDF_F16 ? 2 : 1);
     s->nb = hyb::i8_blocks(s->n);
+    *bytes = count * elem;
     HYB_TRY(hipMalloc(&s->store, count * elem));
     if (s->fmt == HYB_SDF_I8_BRICK)
         HYB_TRY(hipMalloc(&s->scales, sizeof(float) * static_cast<size_t>(s->nb) * s->nb * s->nb));
-    return from_hip(hyb::launch_quantize(fmt, s->values, s->n, s->store, s->scales, stream));
+    return HYB_OK;
+}
+
+// Writes the kernels' copy of the FP32 samples in s->values (storage format,
+// bricked layout); for the compact formats the dequantized values replace
+// s->values in place.
+inline hyb_status quantize(hyb_sdf_s* s, hipStream_t stream) {
+    return from_hip(hyb::launch_quantize(s->layout, s->values, s->n, s->store, s->scales, stream));
 }
 
 inline bool valid_fmt(hyb_sdf_format f) { return f == HYB_SDF_F32 || f == HYB_SDF_F16 || f == HYB_SDF_I8_BRICK; }

@@ -98,16 +98,29 @@ hipError_t launch_df_backward(const TraceArgs& a, const float* t_hit, const floa
 hipError_t launch_entries(const float4* nodes4, const float4* tris, int64_t n_nodes, const EntryGrid& g,
                           int32_t* entry, hipStream_t stream);
 
+// Adds to *sum (zero before) a hash of the mesh's boundary: it stays 0 when the
+// triangles form closed surfaces.
+hipError_t launch_mesh_boundary(const float4* tris, int64_t n_tris, unsigned long long* sum, hipStream_t stream);
+
 struct SdfBuildArgs {
-    const float4* nodes;
+    const float4* nodes4;
     const float4* tris;
+    const unsigned long long* boundary;  // of launch_mesh_boundary
     int32_t n_grid;
     float lo_x, lo_y, lo_z, h;
     int32_t exterior_solid;
     float* out;  // n^3 floats, x fastest
+    // set by launch_sdf_build, in the scratch: the nodes whose winding number
+    // is found, and every node's component (its listed node within the tile)
+    uint32_t* count;
+    uint32_t* list;
+    uint16_t* label;
 };
 
-hipError_t launch_sdf_build(const SdfBuildArgs& a, hipStream_t stream);
+// Signed distances of an n_grid^3 grid; `scratch` is device memory of at least
+// sdf_build_scratch(n_grid) bytes, free again once the work has completed.
+size_t sdf_build_scratch(int32_t n);
+hipError_t launch_sdf_build(const SdfBuildArgs& a, void* scratch, size_t scratch_bytes, hipStream_t stream);
 
 // Per-block maxima of the cell Lipschitz bounds and of the per-axis cell
 // slopes of an n^3 grid (x fastest), and a flag for non-finite samples: block

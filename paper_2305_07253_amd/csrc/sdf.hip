@@ -1,22 +1,10 @@
-// Distance-field construction from the triangle BVH (build time, not the hot
-// path): one thread per grid node computes the exact signed distance in FP64
-// (sdf_node_value) and rounds it once to FP32; a second kernel reduces the
-// Lipschitz bound of the stored grid.
+// The stored forms of a grid and its step bounds: the kernels' bricked copy in
+// each format, and the reductions of the Lipschitz and slope bounds.
+#include "hyb_device.hpp"
 #include "kernels.hpp"
-#include "sdf_device.hpp"
 
 namespace hyb {
 namespace {
-
-__global__ __launch_bounds__(256) void k_sdf_build(SdfBuildArgs a) {
-    const int64_t n = a.n_grid;
-    const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (id >= n * n * n) return;
-    const int64_t i = id % n, j = (id / n) % n, k = id / (n * n);
-    const D3 p = d3((double)a.lo_x + (double)i * (double)a.h, (double)a.lo_y + (double)j * (double)a.h,
-                    (double)a.lo_z + (double)k * (double)a.h);
-    a.out[id] = (float)sdf_node_value(a.nodes, a.tris, p, a.exterior_solid);
-}
 
 // Largest cell gradient bound of the grid (cell_lipschitz) and largest
 // per-axis slopes (cell_slopes), and whether any sample is not finite (fmaxf
@@ -174,13 +162,6 @@ hipError_t launch_quantize(int fmt, float* values, int32_t n, void* out, float* 
     } else {
         return hipErrorInvalidValue;
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_sdf_build(const SdfBuildArgs& a, hipStream_t stream) {
-    const int64_t total = (int64_t)a.n_grid * a.n_grid * a.n_grid;
-    const int64_t blocks = (total + 255) / 256;
-    hipLaunchKernelGGL(k_sdf_build, dim3((unsigned)blocks), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -1,5 +1,8 @@
-// Exact signed distance at one grid node (internal header): the per-node body
-// of the distance-field build kernel, host+device so a CPU build can check it.
+// Exact signed distance at one grid node (internal header), host+device so a
+// CPU build can check it: the distance of a point to a triangle, the signed
+// crossing of a ray with one, and, as the definition of a node's value, a query
+// of one point that uses them.  The build kernels (sdf_build.hip) evaluate the
+// same two functions over many nodes at once.
 //   distance  nearest-triangle query over the BVH in FP64: children in order of
 //             their box distance, a subtree skipped once its box is no closer
 //             than the best triangle; point/triangle distance = plane distance
@@ -26,32 +29,44 @@ HYB_HD D3 dcross(D3 a, D3 b) {
 }
 HYB_HD D3 dvert(float4 v) { return d3(v.x, v.y, v.z); }
 
-// squared distance from p to the segment [a, b]
-HYB_HD double seg_dist2(D3 p, D3 a, D3 b) {
-    const D3 e = dsub(b, a), w = dsub(p, a);
-    const double ee = ddot(e, e);
-    double s = ee > 0.0 ? ddot(w, e) / ee : 0.0;
-    s = s < 0.0 ? 0.0 : (s > 1.0 ? 1.0 : s);
-    const D3 r = d3(w.x - s * e.x, w.y - s * e.y, w.z - s * e.z);
+// Reciprocal within a few units in the last place, for positive normal x
+// (exact division in the CPU build).
+HYB_HD double rcp64(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double r = __builtin_amdgcn_rcp(x);
+    return fma(fma(-x, r, 1.0), r, r);
+#else
+    return 1.0 / x;
+#endif
+}
+
+// squared length of w - s e at the s in [0, 1] that makes it least, with
+// ee = e . e and we = w . e: the distance from a point w off the start of an
+// edge e.  An error of s enters only squared (s is at the minimum), so the
+// reciprocal need not be rounded correctly.
+HYB_HD double edge_dist2(D3 w, D3 e, double ee, double we) {
+    double s = ee > 0.0 ? we * rcp64(ee) : 0.0;
+    s = fmin(fmax(s, 0.0), 1.0);
+    const D3 r = d3(fma(-s, e.x, w.x), fma(-s, e.y, w.y), fma(-s, e.z, w.z));
     return ddot(r, r);
 }
 
-// squared distance from p to triangle abc
+// squared distance from p to triangle abc: to its plane when the projection of
+// p lies inside (barycentric coordinates times det, from the Gram matrix of two
+// edges; a rounding error there moves the border by as little, where both
+// distances agree to second order), else to the nearest edge
 HYB_HD double tri_dist2(D3 p, D3 a, D3 b, D3 c) {
-    const D3 n = dcross(dsub(b, a), dsub(c, a));
+    const D3 e = dsub(b, a), f = dsub(c, a), w = dsub(p, a);
+    const double ee = ddot(e, e), ef = ddot(e, f), ff = ddot(f, f), we = ddot(w, e), wf = ddot(w, f);
+    const double u = ff * we - ef * wf, v = ee * wf - ef * we;
+    const D3 n = dcross(e, f);
     const double nn = ddot(n, n);
-    if (nn > 0.0) {
-        // the projection of p lies inside iff p is on the inner side of all
-        // three edge planes (each contains an edge and the normal)
-        const bool in_ab = ddot(dcross(dsub(b, a), dsub(p, a)), n) >= 0.0;
-        const bool in_bc = ddot(dcross(dsub(c, b), dsub(p, b)), n) >= 0.0;
-        const bool in_ca = ddot(dcross(dsub(a, c), dsub(p, c)), n) >= 0.0;
-        if (in_ab && in_bc && in_ca) {
-            const double h = ddot(dsub(p, a), n);
-            return h * h / nn;
-        }
+    if (u >= 0.0 && v >= 0.0 && u + v <= ee * ff - ef * ef && nn > 0.0) {
+        const double h = ddot(w, n), hh = h * h, r = rcp64(nn), q = hh * r;
+        return fma(fma(-q, nn, hh), r, q);
     }
-    return fmin(seg_dist2(p, a, b), fmin(seg_dist2(p, b, c), seg_dist2(p, c, a)));
+    const D3 g = dsub(c, b), x = dsub(p, b);
+    return fmin(edge_dist2(w, e, ee, we), fmin(edge_dist2(w, f, ff, wf), edge_dist2(x, g, ddot(g, g), ddot(x, g))));
 }
 
 HYB_HD double box_dist2(D3 p, float lx, float hx, float ly, float hy, float lz, float hz) {
