@@ -1,6 +1,6 @@
 // Trace kernels: the combined query and the two pure baselines.
 //
-// One ray per lane.  Rays and hits are SoA arrays, so each of the seven input
+// One ray per lane (in small launches, several lanes per ray).  Rays and hits are SoA arrays, so each of the seven input
 // and four output streams is read or written with fully coalesced 256-byte
 // wavefront accesses.  The BVH stack lives in LDS ([depth][thread] so the 64
 // lanes of a wavefront hit 64 distinct banks), with a small private spill area
@@ -9,6 +9,28 @@
 #include "kernels.hpp"
 
 namespace hyb {
+
+// Rays of a wavefront, as a power of two: 64, and fewer for a launch that would
+// leave most of the chip idle.  Such a launch lasts as long as its slowest
+// wavefront, which runs every path that any of its rays takes; with fewer rays
+// each it runs fewer, on SIMDs that had nothing to do.  A wavefront of 2^k rays
+// traces each in 64 >> k lanes alike (same instructions, same loads, same
+// values stored), because wavefronts with few active lanes on an otherwise idle
+// SIMD issue vector instructions at a quarter of the rate.
+// Up to 2,048 wavefronts that way (two per SIMD): 1,000 rays of the small room
+// at threshold 1 44 -> 25 us, triangles only 45 -> 24 us, of the GI scene 61 ->
+// 30 and 103 -> 46 us; at 16,384 rays 78 -> 72 and 102 -> 78 us, at 65,536 92 ->
+// 85 and 118 -> 105 us, at 262,144 (64 rays each already) 32 rays would take 146
+// for 113 us.  The distance field alone diverges less: to 1,024 wavefronts and
+// 8,192 rays (1,000 rays 29 -> 25 us, 4,096 34 -> 27 us), 16,384 rays took 3 to
+// 5% longer.
+static uint32_t rays_shift(int mode, int64_t n) {
+    if (mode == kDfOnly && n > 8192) return 6;
+    const int64_t waves = mode == kDfOnly ? 1024 : 2048;
+    uint32_t shift = 0;
+    while (shift < 6 && n > (waves << shift)) ++shift;
+    return shift;
+}
 
 // Wavefronts per SIMD the compiler is held to where that measured faster:
 // one-cell F16 bricks, 74 VGPRs left alone, fit seven at 72; the combined I8
@@ -23,9 +45,10 @@ constexpr int trace_waves() {
 
 template <int MODE, int FMT, bool COUNT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(trace_waves<MODE, FMT, COUNT>())))
-void k_trace(TraceArgs a) {
+void k_trace(TraceArgs a, uint32_t shift) {
     extern __shared__ int s_stack[];
-    const int64_t i = (int64_t)xcd_block(blockIdx.x, gridDim.x, a.xcd_run) * kBlock + threadIdx.x;
+    const int64_t i = ((int64_t)xcd_block(blockIdx.x, gridDim.x, a.xcd_run) << shift) +
+                      (threadIdx.x & ((1u << shift) - 1));
     if (i >= a.n) return;
     trace_ray<MODE, FMT, COUNT>(a, i, s_stack + threadIdx.x, kBlock);
 }
@@ -33,8 +56,9 @@ void k_trace(TraceArgs a) {
 template <int MODE, int FMT, bool COUNT>
 static hipError_t launch(const TraceArgs& a, hipStream_t stream) {
     const size_t lds = MODE == kDfOnly ? 0 : sizeof(int) * kLdsDepth * kBlock;
-    const int64_t blocks = (a.n + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL((k_trace<MODE, FMT, COUNT>), dim3((unsigned)blocks), dim3(kBlock), lds, stream, a);
+    const uint32_t shift = rays_shift(MODE, a.n);
+    const int64_t blocks = (a.n + (int64_t(1) << shift) - 1) >> shift;
+    hipLaunchKernelGGL((k_trace<MODE, FMT, COUNT>), dim3((unsigned)blocks), dim3(kBlock), lds, stream, a, shift);
     return hipGetLastError();
 }
 
