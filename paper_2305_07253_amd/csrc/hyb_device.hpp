@@ -193,84 +193,182 @@ HYB_HD void order2(float& ka, int& ra, float& kb, int& rb) {
     ra = r;
 }
 
+// A four-wide node's children against a ray: their references, and the keys by
+// which they are ordered (where the ray enters the box), +inf for boxes that it
+// misses on [seg_lo, hi].
+struct Children {
+    float k0, k1, k2, k3;
+    int r0, r1, r2, r3;
+};
+
+HYB_HD Children test_children(const float4* __restrict__ nodes, int ref, const BoxRay& br, float seg_lo, float hi) {
+    const float4* n = nodes + 8 * (int64_t)ref;
+    const float4 lx = n[0], hx = n[1], ly = n[2], hy = n[3], lz = n[4], hz = n[5], rf = n[6];
+    constexpr float kNone = __builtin_inff();
+    Children c;
+    float tn, tf;
+    box_clip(br, lx.x, hx.x, ly.x, hy.x, lz.x, hz.x, seg_lo, hi, tn, tf);
+    c.k0 = tn <= tf ? tn : kNone;
+    box_clip(br, lx.y, hx.y, ly.y, hy.y, lz.y, hz.y, seg_lo, hi, tn, tf);
+    c.k1 = tn <= tf ? tn : kNone;
+    box_clip(br, lx.z, hx.z, ly.z, hy.z, lz.z, hz.z, seg_lo, hi, tn, tf);
+    c.k2 = tn <= tf ? tn : kNone;
+    box_clip(br, lx.w, hx.w, ly.w, hy.w, lz.w, hz.w, seg_lo, hi, tn, tf);
+    c.k3 = tn <= tf ? tn : kNone;
+    c.r0 = bits_i(rf.x);
+    c.r1 = bits_i(rf.y);
+    c.r2 = bits_i(rf.z);
+    c.r3 = bits_i(rf.w);
+    return c;
+}
+
+// The same through each box's planes as the ray meets them: with the byte offset
+// of the near plane's column known from the sign of 1 / d (0 or 16), the two slab
+// distances of an axis need no minimum and maximum.  The values are the same
+// ((lo - o) / d <= (hi - o) / d for d > 0, also after rounding, and the reverse
+// for d < 0).
+struct NearPlanes {
+    uint32_t x, y, z;
+};
+
+HYB_HD NearPlanes near_planes(const RayInv& inv) {
+    return {inv.x < 0.0f ? 16u : 0u, inv.y < 0.0f ? 16u : 0u, inv.z < 0.0f ? 16u : 0u};
+}
+
+HYB_HD void planes_clip(const BoxRay& r, float nx, float fx, float ny, float fy, float nz, float fz, float seg_lo,
+                        float seg_hi, float& tn, float& tf) {
+    tn = fmaxf(fmaxf((nx - r.ox) * r.ix, (ny - r.oy) * r.iy), fmaxf((nz - r.oz) * r.iz, seg_lo));
+    tf = fminf(fminf((fx - r.ox) * r.ix, (fy - r.oy) * r.iy), fminf((fz - r.oz) * r.iz, seg_hi)) * kBoxPad;
+}
+
+HYB_HD Children test_children(const float4* __restrict__ nodes, int ref, const BoxRay& br, const NearPlanes& near,
+                              float seg_lo, float hi) {
+    const char* n = reinterpret_cast<const char*>(nodes + 8 * (int64_t)ref);
+    const auto column = [&](uint32_t at) { return *reinterpret_cast<const float4*>(n + at); };
+    const float4 nx = column(near.x), fx = column(near.x ^ 16u), ny = column(32u + near.y),
+                 fy = column(32u + (near.y ^ 16u)), nz = column(64u + near.z), fz = column(64u + (near.z ^ 16u)),
+                 rf = column(96u);
+    constexpr float kNone = __builtin_inff();
+    Children c;
+    float tn, tf;
+    planes_clip(br, nx.x, fx.x, ny.x, fy.x, nz.x, fz.x, seg_lo, hi, tn, tf);
+    c.k0 = tn <= tf ? tn : kNone;
+    planes_clip(br, nx.y, fx.y, ny.y, fy.y, nz.y, fz.y, seg_lo, hi, tn, tf);
+    c.k1 = tn <= tf ? tn : kNone;
+    planes_clip(br, nx.z, fx.z, ny.z, fy.z, nz.z, fz.z, seg_lo, hi, tn, tf);
+    c.k2 = tn <= tf ? tn : kNone;
+    planes_clip(br, nx.w, fx.w, ny.w, fy.w, nz.w, fz.w, seg_lo, hi, tn, tf);
+    c.k3 = tn <= tf ? tn : kNone;
+    c.r0 = bits_i(rf.x);
+    c.r1 = bits_i(rf.y);
+    c.r2 = bits_i(rf.z);
+    c.r3 = bits_i(rf.w);
+    return c;
+}
+
+// Sorting network, nearest first; misses (+inf) sink to the end.
+HYB_HD void sort_children(Children& c) {
+    order2(c.k0, c.r0, c.k1, c.r1);
+    order2(c.k2, c.r2, c.k3, c.r3);
+    order2(c.k0, c.r0, c.k2, c.r2);
+    order2(c.k1, c.r1, c.k3, c.r3);
+    order2(c.k1, c.r1, c.k2, c.r2);
+}
+
+// This lane's traversal stack of sp entries: the first LDS of them in LDS,
+// `stride` ints apart (one slot per thread of the block, no bank conflicts), the
+// others in a private spill area.  (Variables of the traversal, not a struct: the
+// spill area is indexed, and would take sp to private memory with it.)
+template <int LDS>
+HYB_HD void push_ref(int* lds, int stride, int* spill, int& sp, int ref) {
+    static_assert(LDS > 0 && LDS < kStackDepth, "LDS part of the stack out of range");
+    if (sp < LDS) lds[sp * stride] = ref;
+    else spill[sp - LDS] = ref;
+    ++sp;
+}
+
+template <int LDS>
+HYB_HD int pop_ref(const int* lds, int stride, const int* spill, int& sp) {
+    --sp;
+    return sp < LDS ? lds[sp * stride] : spill[sp - LDS];
+}
+
+// One triangle against the closest hit so far; whether it is hit.  Equal t goes
+// to the smallest original triangle id, independent of traversal order.
+HYB_HD bool closer_triangle(const float4* __restrict__ tp, const ShearRay& sr, float ox, float oy, float oz,
+                            float seg_lo, Hit& best) {
+    const float4 v0 = tp[0], v1 = tp[1], v2 = tp[2];
+    float t, u, v;
+    if (!tri_hit(sr, ox, oy, oz, v0, v1, v2, seg_lo, best.t, t, u, v)) return false;
+    const int id = bits_i(v0.w);
+    if (t < best.t || best.prim < 0 || id < best.prim) {
+        best.t = t;
+        best.prim = id;
+        best.u = u;
+        best.v = v;
+    }
+    return true;
+}
+
 // Closest triangle hit on [seg_lo, seg_hi] (both inclusive) through the
-// four-wide BVH (nodes4 layout, 128-byte nodes).  Equal t goes to the smallest
-// original triangle id, independent of traversal order.  With ANY the
-// traversal stops at the first intersection it finds (any-hit).  With `sort`
-// the children a node's ray hits are visited nearest first (the nearest is
-// entered, the others are pushed farthest first), which lets a closest hit
-// prune farther boxes early on long segments; without it they go in slot
-// order, which costs fewer instructions and gives the same hit (the order
-// only changes which boxes a closer hit prunes, never the result).  `stack`
-// points at this lane's first LDS slot; consecutive entries are `stride` ints
-// apart (one slot per thread of the block, no bank conflicts); entries beyond
-// LDS go to a private spill area.
-template <bool COUNT, bool ANY = false, int LDS = kLdsDepth>
+// four-wide BVH (nodes4 layout, 128-byte nodes).  With ANY the traversal stops
+// at the first intersection it finds (any-hit).  With `sort` the children a
+// node's ray hits are visited nearest first (the nearest is entered, the others
+// are pushed farthest first), which lets a closest hit prune farther boxes early
+// on long segments; without it they go in slot order, which costs fewer
+// instructions and gives the same hit (the order only changes which boxes a
+// closer hit prunes, never the result).
+//
+// For short segments.  The loop's two ways round (a child entered, and a leaf or
+// an entry taken from the stack) become an inner and an outer loop: a wavefront
+// goes down until no lane finds a child, then tests leaves together, which suits
+// segments of a few nodes and one or two leaves that the lanes reach together.
+// Measured against bvh_closest_long's steps on them: 383 against 388 us (GI,
+// threshold 1), 191 against 197 us (shadow rays).
+//
+// PLANES: boxes through near_planes.  Short occlusion rays through F16 147 -> 140
+// us, shadow rays 191 -> 189, 12 scenes in one launch 515 -> 508; the combined
+// query of two-cell bricks, whose march needs more registers at once, is left at
+// the plain test (72 VGPRs either way: FP32 382 us against 392 through
+// near_planes, F16 at 220^3 274 against 284).
+template <bool COUNT, bool ANY = false, int LDS = kLdsDepth, bool PLANES = true>
 HYB_HD Hit bvh_closest(const float4* __restrict__ nodes, const float4* __restrict__ tris,
                        float ox, float oy, float oz, float dx, float dy, float dz, const RayInv& inv,
-                       float seg_lo, float seg_hi, int* stack, int stride, Counters& cnt, int start = 0,
+                       float seg_lo, float seg_hi, int* lds, int stride, Counters& cnt, int start = 0,
                        bool sort = true) {
-    Hit best;
-    best.t = seg_hi;
-    best.prim = -1;
-    best.u = 0.0f;
-    best.v = 0.0f;
+    Hit best = {seg_hi, -1, 0.0f, 0.0f};
     const BoxRay br = {ox, oy, oz, inv.x, inv.y, inv.z};
+    const NearPlanes near = near_planes(inv);
     const ShearRay sr = make_shear(dx, dy, dz);
-    static_assert(LDS > 0 && LDS < kStackDepth, "LDS part of the stack out of range");
     int spill[kStackDepth - LDS];
     int sp = 0;
     int ref = start;  // the root, or a subtree holding every triangle the segment can reach
     for (;;) {
         if (ref >= 0) {
-            const float4* n = nodes + 8 * (int64_t)ref;
-            const float4 lx = n[0], hx = n[1], ly = n[2], hy = n[3], lz = n[4], hz = n[5], rf = n[6];
             if (COUNT) cnt.nodes++;
-            const float hi = best.t * kBoxPad;
             constexpr float kNone = __builtin_inff();
-            float tn, tf;
-            box_clip(br, lx.x, hx.x, ly.x, hy.x, lz.x, hz.x, seg_lo, hi, tn, tf);
-            float k0 = tn <= tf ? tn : kNone;
-            box_clip(br, lx.y, hx.y, ly.y, hy.y, lz.y, hz.y, seg_lo, hi, tn, tf);
-            float k1 = tn <= tf ? tn : kNone;
-            box_clip(br, lx.z, hx.z, ly.z, hy.z, lz.z, hz.z, seg_lo, hi, tn, tf);
-            float k2 = tn <= tf ? tn : kNone;
-            box_clip(br, lx.w, hx.w, ly.w, hy.w, lz.w, hz.w, seg_lo, hi, tn, tf);
-            float k3 = tn <= tf ? tn : kNone;
-            int r0 = bits_i(rf.x), r1 = bits_i(rf.y), r2 = bits_i(rf.z), r3 = bits_i(rf.w);
+            const float hi = best.t * kBoxPad;
+            Children c = PLANES ? test_children(nodes, ref, br, near, seg_lo, hi)
+                                : test_children(nodes, ref, br, seg_lo, hi);
             if (sort) {
-                // sorting network, nearest first; misses (+inf) sink to the end
-                order2(k0, r0, k1, r1);
-                order2(k2, r2, k3, r3);
-                order2(k0, r0, k2, r2);
-                order2(k1, r1, k3, r3);
-                order2(k1, r1, k2, r2);
-                if (k0 < kNone) {
-                    const int push[3] = {r3, r2, r1};
-                    const bool take[3] = {k3 < kNone, k2 < kNone, k1 < kNone};
-                    for (int c = 0; c < 3; ++c) {
-                        if (!take[c]) continue;
-                        if (sp < LDS) stack[sp * stride] = push[c];
-                        else spill[sp - LDS] = push[c];
-                        ++sp;
-                    }
-                    ref = r0;
+                sort_children(c);
+                if (c.k0 < kNone) {
+                    if (c.k3 < kNone) push_ref<LDS>(lds, stride, spill, sp, c.r3);
+                    if (c.k2 < kNone) push_ref<LDS>(lds, stride, spill, sp, c.r2);
+                    if (c.k1 < kNone) push_ref<LDS>(lds, stride, spill, sp, c.r1);
+                    ref = c.r0;
                     continue;
                 }
             } else {
                 // slot order: enter the first child hit, push the others
-                const int rr[4] = {r3, r2, r1, r0};
-                const bool hh[4] = {k3 < kNone, k2 < kNone, k1 < kNone, k0 < kNone};
+                const int rr[4] = {c.r3, c.r2, c.r1, c.r0};
+                const bool hh[4] = {c.k3 < kNone, c.k2 < kNone, c.k1 < kNone, c.k0 < kNone};
                 int next = 0;
                 bool have = false;
-                for (int c = 0; c < 4; ++c) {
-                    if (!hh[c]) continue;
-                    if (have) {
-                        if (sp < LDS) stack[sp * stride] = next;
-                        else spill[sp - LDS] = next;
-                        ++sp;
-                    }
-                    next = rr[c];
+                for (int k = 0; k < 4; ++k) {
+                    if (!hh[k]) continue;
+                    if (have) push_ref<LDS>(lds, stride, spill, sp, next);
+                    next = rr[k];
                     have = true;
                 }
                 if (have) {
@@ -282,25 +380,93 @@ HYB_HD Hit bvh_closest(const float4* __restrict__ nodes, const float4* __restric
             const int info = ~ref;
             const int first = info >> 3, count = info & 7;
             for (int k = 0; k < count; ++k) {
-                const float4* tp = tris + 3 * (int64_t)(first + k);
-                const float4 v0 = tp[0], v1 = tp[1], v2 = tp[2];
                 if (COUNT) cnt.tris++;
-                float t, u, v;
-                if (tri_hit(sr, ox, oy, oz, v0, v1, v2, seg_lo, best.t, t, u, v)) {
-                    const int id = bits_i(v0.w);
-                    if (t < best.t || best.prim < 0 || id < best.prim) {
-                        best.t = t;
-                        best.prim = id;
-                        best.u = u;
-                        best.v = v;
-                    }
-                    if (ANY) return best;
-                }
+                if (closer_triangle(tris + 3 * (int64_t)(first + k), sr, ox, oy, oz, seg_lo, best) && ANY) return best;
             }
         }
         if (sp == 0) break;
-        --sp;
-        ref = sp < LDS ? stack[sp * stride] : spill[sp - LDS];
+        ref = pop_ref<LDS>(lds, stride, spill, sp);
+    }
+    if (best.prim < 0) best.t = __builtin_inff();
+    return best;
+}
+
+// Whether a wavefront's lanes (of those still traversing) take a triangle step:
+// once a quarter of them are at leaves.  Counted over the GI rays' own visits at
+// 145 vector instructions a node and 80 a triangle, a quarter costs 10,700 per
+// wavefront, an eighth 11,200, three eighths 11,200, half 11,900, and steps of
+// both kinds 13,500.
+HYB_HD bool triangle_step(bool at_leaf) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return 4 * __popcll(__ballot(at_leaf)) >= __popcll(__ballot(true));
+#else
+    return at_leaf;
+#endif
+}
+
+// Where all lanes of a wavefront that run a loop meet at the end of its body.
+// Without it the compiler gives each path its own way back to the top, as an
+// inner loop that its lanes go round until none of them takes that path, while
+// the others wait.
+HYB_HD void meet() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_wave_barrier();
+#endif
+}
+
+// The same hit (nearest children first) for long segments.  Bound by VALU issue
+// under divergence.  A wavefront's step is either a node for its lanes at nodes
+// or one triangle for its lanes at leaves, as they vote (triangle_step), and all
+// lanes meet after each: the others wait, so both kinds of step run with more
+// lanes.  Each lane makes the visits of bvh_closest in the same order.
+// Triangles only, 518,400 GI rays: 274 -> 214 us against bvh_closest, 193 us with
+// the boxes through near_planes (2,073,600 rays 838 -> 590 us, 15,300 -> 9,900
+// vector instructions a wavefront); without the meeting point 328 us.
+template <bool COUNT, bool ANY = false, int LDS = kLdsDepth>
+HYB_HD Hit bvh_closest_long(const float4* __restrict__ nodes, const float4* __restrict__ tris,
+                            float ox, float oy, float oz, float dx, float dy, float dz, const RayInv& inv,
+                            float seg_lo, float seg_hi, int* lds, int stride, Counters& cnt, int start = 0) {
+    Hit best = {seg_hi, -1, 0.0f, 0.0f};
+    const BoxRay br = {ox, oy, oz, inv.x, inv.y, inv.z};
+    const NearPlanes near = near_planes(inv);
+    const ShearRay sr = make_shear(dx, dy, dz);
+    int spill[kStackDepth - LDS];
+    int sp = 0;
+    int ref = start;
+    bool live = true;
+    while (live) {
+        bool pop = false;
+        if (triangle_step(ref < 0)) {
+            if (ref < 0) {
+                // the next triangle of the leaf, which goes on as what is left of it
+                const int info = ~ref;
+                const int first = info >> 3, count = info & 7;
+                if (count > 0) {
+                    if (COUNT) cnt.tris++;
+                    if (closer_triangle(tris + 3 * (int64_t)first, sr, ox, oy, oz, seg_lo, best) && ANY) return best;
+                }
+                ref = ~(info + 7);  // one triangle on, one fewer
+                pop = count <= 1;
+            }
+        } else if (ref >= 0) {
+            if (COUNT) cnt.nodes++;
+            constexpr float kNone = __builtin_inff();
+            Children c = test_children(nodes, ref, br, near, seg_lo, best.t * kBoxPad);
+            sort_children(c);
+            if (c.k0 < kNone) {
+                if (c.k3 < kNone) push_ref<LDS>(lds, stride, spill, sp, c.r3);
+                if (c.k2 < kNone) push_ref<LDS>(lds, stride, spill, sp, c.r2);
+                if (c.k1 < kNone) push_ref<LDS>(lds, stride, spill, sp, c.r1);
+                ref = c.r0;
+            } else {
+                pop = true;
+            }
+        }
+        if (pop) {
+            live = sp > 0;
+            if (live) ref = pop_ref<LDS>(lds, stride, spill, sp);
+        }
+        meet();
     }
     if (best.prim < 0) best.t = __builtin_inff();
     return best;
@@ -976,6 +1142,9 @@ HYB_HD int entry_node(const TraceArgs& a, float ox, float oy, float oz, float dx
 // nearest-first order prunes little and costs a sorting network per node).
 constexpr float kShortSegment = 4.0f;
 
+// tau_end is 0 but for shadow queries.
+HYB_HD bool short_segments(const TraceArgs& a) { return a.tau <= kShortSegment && a.tau_end <= kShortSegment; }
+
 // The grid of a query's arguments, with the step bounds of a deferred
 // update read from the device (uniform loads) where the arguments point at
 // them.
@@ -996,8 +1165,25 @@ HYB_HD Grid grid_of(const TraceArgs& a) {
 // part of every query reports NaN (prim -2) until the next update.
 HYB_HD bool df_unusable(const TraceArgs& a) { return a.bounds && a.bounds[kBBad] != 0.0f; }
 
+// Which traversal a query's triangle segments take: known where the kernel is
+// chosen (kShortSegments, kLongSegments), or per ray (kAnySegments: the batch,
+// whose scenes differ).
+enum Segments : int { kAnySegments = 0, kShortSegments = 1, kLongSegments = 2 };
+
+template <int SEG, bool COUNT, bool ANY, int LDS, bool PLANES = true>
+HYB_HD Hit bvh_segment(const TraceArgs& a, float ox, float oy, float oz, float dx, float dy, float dz,
+                       const RayInv& inv, float t0, float t1, int* stack, int stride, Counters& cnt, bool sort) {
+    const int start = entry_node(a, ox, oy, oz, dx, dy, dz, t0, t1);
+    if constexpr (SEG == kLongSegments)
+        return bvh_closest_long<COUNT, ANY, LDS>(a.nodes, a.tris, ox, oy, oz, dx, dy, dz, inv, t0, t1, stack, stride,
+                                                 cnt, start);
+    else
+        return bvh_closest<COUNT, ANY, LDS, PLANES>(a.nodes, a.tris, ox, oy, oz, dx, dy, dz, inv, t0, t1, stack,
+                                                    stride, cnt, start, SEG == kAnySegments && sort);
+}
+
 // One ray of a query (the body of the trace kernels).
-template <int MODE, int FMT, bool COUNT, int LDS = kLdsDepth>
+template <int MODE, int FMT, bool COUNT, int LDS = kLdsDepth, int SEG = kAnySegments>
 HYB_HD void trace_ray(const TraceArgs& a, int64_t i, int* stack, int stride) {
     const float ox = a.ox[i], oy = a.oy[i], oz = a.oz[i];
     const float dx = a.dx[i], dy = a.dy[i], dz = a.dz[i];
@@ -1015,9 +1201,8 @@ HYB_HD void trace_ray(const TraceArgs& a, int64_t i, int* stack, int stride) {
             hit.t = __builtin_nanf("");
             hit.prim = -2;
         } else if (MODE == kBvhOnly) {
-            hit = bvh_closest<COUNT, false, LDS>(a.nodes, a.tris, ox, oy, oz, dx, dy, dz, ray_inv(dx, dy, dz), tmin,
-                                                 tmax, stack, stride, cnt,
-                                                 entry_node(a, ox, oy, oz, dx, dy, dz, tmin, tmax));
+            hit = bvh_segment<kLongSegments, COUNT, false, LDS>(a, ox, oy, oz, dx, dy, dz, ray_inv(dx, dy, dz), tmin,
+                                                                tmax, stack, stride, cnt, true);
         } else if (MODE == kDfOnly) {
             const float t = df_first_root<FMT, COUNT>(g, ox, oy, oz, dx, dy, dz, ray_inv(dx, dy, dz), tmin, tmax, cnt);
             if (t != __builtin_inff()) {  // NaN: see df_first_root
@@ -1030,7 +1215,7 @@ HYB_HD void trace_ray(const TraceArgs& a, int64_t i, int* stack, int stride) {
             // runs first (Section 2, out-of-order any-hit processing).
             const float t1 = fminf(fmaf(a.tau, a.h, tmin), tmax);
             const float t2 = fmaxf(fmaf(-a.tau_end, a.h, tmax), t1);
-            const bool sort = !(a.tau <= kShortSegment && a.tau_end <= kShortSegment);
+            const bool sort = !short_segments(a);
             if (t2 > t1 || (a.tau == 0.0f && a.tau_end == 0.0f)) {
                 const float t = df_first_root<FMT, COUNT>(g, ox, oy, oz, dx, dy, dz, ray_inv(dx, dy, dz), t1, t2, cnt);
                 if (t != __builtin_inff()) {  // NaN: see df_first_root
@@ -1039,13 +1224,11 @@ HYB_HD void trace_ray(const TraceArgs& a, int64_t i, int* stack, int stride) {
                 }
             }
             if (hit.prim == -1 && t1 > tmin)
-                hit = bvh_closest<COUNT, true, LDS>(a.nodes, a.tris, ox, oy, oz, dx, dy, dz, ray_inv(dx, dy, dz), tmin,
-                                                    t1, stack, stride, cnt,
-                                                    entry_node(a, ox, oy, oz, dx, dy, dz, tmin, t1), sort);
+                hit = bvh_segment<SEG, COUNT, true, LDS>(a, ox, oy, oz, dx, dy, dz, ray_inv(dx, dy, dz), tmin, t1,
+                                                         stack, stride, cnt, sort);
             if (hit.prim == -1 && tmax > t2)
-                hit = bvh_closest<COUNT, true, LDS>(a.nodes, a.tris, ox, oy, oz, dx, dy, dz, ray_inv(dx, dy, dz), t2,
-                                                    tmax, stack, stride, cnt,
-                                                    entry_node(a, ox, oy, oz, dx, dy, dz, t2, tmax), sort);
+                hit = bvh_segment<SEG, COUNT, true, LDS>(a, ox, oy, oz, dx, dy, dz, ray_inv(dx, dy, dz), t2, tmax,
+                                                         stack, stride, cnt, sort);
         } else {
             // Eq. (2) with two sub-queries processed in order (first hit):
             // triangles on [tmin, t1]; the distance field on [t1, tmax] only
@@ -1056,9 +1239,8 @@ HYB_HD void trace_ray(const TraceArgs& a, int64_t i, int* stack, int stride) {
             const RayInv inv = ray_inv(dx, dy, dz);
             const float t1 = fminf(fmaf(a.tau, a.h, tmin), tmax);
             if (t1 > tmin)
-                hit = bvh_closest<COUNT, false, LDS>(a.nodes, a.tris, ox, oy, oz, dx, dy, dz, inv, tmin, t1, stack,
-                                                     stride, cnt, entry_node(a, ox, oy, oz, dx, dy, dz, tmin, t1),
-                                                     !(a.tau <= kShortSegment));
+                hit = bvh_segment<SEG, COUNT, false, LDS, !(SEG == kShortSegments && Brick<FMT>::kCells == 2)>(
+                    a, ox, oy, oz, dx, dy, dz, inv, tmin, t1, stack, stride, cnt, !short_segments(a));
             if (hit.prim < 0 && (t1 < tmax || a.tau == 0.0f)) {
                 // I8 forms its solves again (df_resolve, REFORM): seven wavefronts per SIMD
                 const float t = df_first_root<FMT, COUNT, FMT == kI8>(g, ox, oy, oz, dx, dy, dz, inv, t1, tmax, cnt);

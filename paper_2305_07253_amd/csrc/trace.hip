@@ -43,23 +43,35 @@ constexpr int trace_waves() {
     return 1;
 }
 
-template <int MODE, int FMT, bool COUNT>
+template <int MODE, int FMT, bool COUNT, int SEG>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(trace_waves<MODE, FMT, COUNT>())))
 void k_trace(TraceArgs a, uint32_t shift) {
     extern __shared__ int s_stack[];
     const int64_t i = ((int64_t)xcd_block(blockIdx.x, gridDim.x, a.xcd_run) << shift) +
                       (threadIdx.x & ((1u << shift) - 1));
     if (i >= a.n) return;
-    trace_ray<MODE, FMT, COUNT>(a, i, s_stack + threadIdx.x, kBlock);
+    trace_ray<MODE, FMT, COUNT, kLdsDepth, SEG>(a, i, s_stack + threadIdx.x, kBlock);
 }
 
-template <int MODE, int FMT, bool COUNT>
-static hipError_t launch(const TraceArgs& a, hipStream_t stream) {
+template <int MODE, int FMT, bool COUNT, int SEG>
+static hipError_t launch_segments(const TraceArgs& a, hipStream_t stream) {
     const size_t lds = MODE == kDfOnly ? 0 : sizeof(int) * kLdsDepth * kBlock;
     const uint32_t shift = rays_shift(MODE, a.n);
     const int64_t blocks = (a.n + (int64_t(1) << shift) - 1) >> shift;
-    hipLaunchKernelGGL((k_trace<MODE, FMT, COUNT>), dim3((unsigned)blocks), dim3(kBlock), lds, stream, a, shift);
+    hipLaunchKernelGGL((k_trace<MODE, FMT, COUNT, SEG>), dim3((unsigned)blocks), dim3(kBlock), lds, stream, a, shift);
     return hipGetLastError();
+}
+
+// Triangle segments of at most kShortSegment voxels take the traversal for short
+// ones, all others (triangles only among them) the one for long ones.
+template <int MODE, int FMT, bool COUNT>
+static hipError_t launch(const TraceArgs& a, hipStream_t stream) {
+    if constexpr (MODE == kCombined || MODE == kShadow) {
+        if (short_segments(a)) return launch_segments<MODE, FMT, COUNT, kShortSegments>(a, stream);
+        return launch_segments<MODE, FMT, COUNT, kLongSegments>(a, stream);
+    } else {
+        return launch_segments<MODE, FMT, COUNT, kLongSegments>(a, stream);
+    }
 }
 
 template <int MODE, bool COUNT>
