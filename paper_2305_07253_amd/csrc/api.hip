@@ -139,9 +139,7 @@ hyb_status hyb_build_sdf(hyb_bvh bvh, int32_t n, const float* grid4, uint32_t fl
         // the kernels' copy is written last: until then it is the build's scratch
         rc = from_hip(hyb::launch_sdf_build(a, s->store, store_bytes, st));
     }
-    if (rc == HYB_OK) rc = quantize(s, st);
-    if (rc == HYB_OK) rc = from_hip(hipMalloc(&s->dev_bounds, sizeof(float) * hyb::kDeviceBounds));
-    if (rc == HYB_OK) rc = compute_lipschitz(s, st);
+    if (rc == HYB_OK) rc = store_samples(s, s->values, false, st);
     if (rc != HYB_OK) {
         hyb_sdf_destroy(s);
         return rc;
@@ -166,15 +164,10 @@ hyb_status hyb_sdf_from_grid(const float* values, int32_t n, const float* grid4,
     std::memcpy(s->grid4, grid4, sizeof(s->grid4));
     const size_t bytes = sizeof(float) * static_cast<size_t>(n) * n * n;
     if (e == hipSuccess) e = hipMalloc(&s->values, bytes);
-    if (e == hipSuccess) e = hipMemcpyAsync(s->values, values, bytes, hipMemcpyDeviceToDevice, st);
     hyb_status rc = from_hip(e);
     size_t store_bytes = 0;
     if (rc == HYB_OK) rc = allocate_store(s, &store_bytes);
-    // the compact formats would turn a NaN input into a finite code
-    if (rc == HYB_OK && fmt != HYB_SDF_F32) rc = check_finite(s, st);
-    if (rc == HYB_OK) rc = quantize(s, st);
-    if (rc == HYB_OK) rc = from_hip(hipMalloc(&s->dev_bounds, sizeof(float) * hyb::kDeviceBounds));
-    if (rc == HYB_OK) rc = compute_lipschitz(s, st);
+    if (rc == HYB_OK) rc = store_samples(s, values, false, st);
     if (rc != HYB_OK) {
         hyb_sdf_destroy(s);
         return rc;
@@ -187,18 +180,8 @@ hyb_status hyb_sdf_update(hyb_sdf sdf, const float* values, uint32_t flags, void
     if (!sdf || !values || (flags & ~(HYB_SDF_LIPSCHITZ_SAMPLES | HYB_SDF_UPDATE_DEFERRED)) ||
         !same_device(sdf->device))
         return HYB_ERR_INVALID_ARG;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    const size_t bytes = sizeof(float) * static_cast<size_t>(sdf->n) * sdf->n * sdf->n;
     sdf->certified = (flags & HYB_SDF_LIPSCHITZ_SAMPLES) != 0;
-    HYB_TRY(hipMemcpyAsync(sdf->values, values, bytes, hipMemcpyDeviceToDevice, st));
-    if (flags & HYB_SDF_UPDATE_DEFERRED) return deferred_bounds(sdf, st);
-    if (sdf->fmt != HYB_SDF_F32) {
-        // the compact formats would turn a NaN input into a finite code
-        const hyb_status rc = check_finite(sdf, st);
-        if (rc != HYB_OK) return rc;
-    }
-    HYB_TRY(hyb::launch_quantize(sdf->layout, sdf->values, sdf->n, sdf->store, sdf->scales, st));
-    return compute_lipschitz(sdf, st);
+    return store_samples(sdf, values, (flags & HYB_SDF_UPDATE_DEFERRED) != 0, static_cast<hipStream_t>(stream));
 }
 
 hyb_status hyb_sdf_voxel_size(hyb_sdf sdf, float* h) {

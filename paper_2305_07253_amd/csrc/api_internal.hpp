@@ -38,9 +38,9 @@ struct hyb_sdf_s {
     bool certified = false;  // samples are FP32 roundings of a 1-Lipschitz function
     hyb_sdf_format fmt = HYB_SDF_F32;
     int32_t layout = 0;  // the kernels' storage format and brick layout (hyb::SdfFormat)
-    float* blocks = nullptr;  // per-block maxima of the bound pass (kept for updates)
+    float* blocks = nullptr;  // per-block maxima of launch_store (kept for updates)
     uint64_t version = 0;     // bumped whenever the samples and bounds change (batches re-read them)
-    float* dev_bounds = nullptr;  // hyb::kDeviceBounds floats: the bounds of a deferred update
+    float* dev_bounds = nullptr;  // hyb::kDeviceBounds floats: the bounds of the last update
     bool deferred = false;        // the last update was deferred: the kernels read dev_bounds
     void* bwd_ws = nullptr;       // hyb_df_backward's sort buffers, grown on demand
     size_t bwd_ws_bytes = 0;
@@ -73,73 +73,9 @@ inline bool valid_rays(const hyb_rays* r) {
 
 inline bool valid_hits(const hyb_hits* h) { return h && h->t && h->prim && h->u && h->v; }
 
-// The bound pass over s->values (n^3, x fastest) into host maxima m[0..4]
-// (see launch_lipschitz); synchronous.
-inline hyb_status grid_bounds(hyb_sdf_s* s, hipStream_t stream, float m[hyb::kBoundValues]) {
-    constexpr int V = hyb::kBoundValues;
-    const int32_t nb = hyb::lipschitz_blocks(s->n);
-    if (!s->blocks) HYB_TRY(hipMalloc(&s->blocks, sizeof(float) * V * nb));
-    int32_t got = 0;
-    hipError_t e = hyb::launch_lipschitz(s->values, s->n, s->grid4[3], s->blocks, &got, stream);
-    std::vector<float> host(V * static_cast<size_t>(nb), 0.0f);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(host.data(), s->blocks, sizeof(float) * V * nb, hipMemcpyDeviceToHost, stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    HYB_TRY(e);
-    for (int c = 0; c < V; ++c) m[c] = 0.0f;
-    for (size_t b = 0; b < static_cast<size_t>(nb); ++b)
-        for (int c = 0; c < V; ++c) m[c] = std::max(m[c], host[V * b + c]);
-    return HYB_OK;
-}
-
-// HYB_ERR_INVALID_ARG when some sample in s->values is NaN or infinite.
-inline hyb_status check_finite(hyb_sdf_s* s, hipStream_t stream) {
-    float m[hyb::kBoundValues];
-    const hyb_status rc = grid_bounds(s, stream, m);
-    if (rc != HYB_OK) return rc;
-    return m[4] != 0.0f ? HYB_ERR_INVALID_ARG : HYB_OK;
-}
-
-// Lipschitz bound and per-axis slope bounds of the stored grid: per-block
-// maxima on the device, final maxima on the host (build time; synchronous).
-// A stored sample that is not finite (e.g. an F16 overflow) is an error.
-inline hyb_status compute_lipschitz(hyb_sdf_s* s, hipStream_t stream) {
-    float m[hyb::kBoundValues];
-    const hyb_status rc = grid_bounds(s, stream, m);
-    if (rc != HYB_OK) return rc;
-    for (float v : m)
-        if (!std::isfinite(v)) return HYB_ERR_INVALID_ARG;
-    if (m[4] != 0.0f) return HYB_ERR_INVALID_ARG;
-    s->lipschitz = hyb::finish_lipschitz(m[0]);
-    for (int c = 0; c < 3; ++c) s->slope[c] = hyb::finish_slope(m[1 + c]);
-    s->deferred = false;
-    ++s->version;
-    return HYB_OK;
-}
-
 // The certified-grid step slack of the kernels, or +inf.
 inline float two_e_of(const hyb_sdf_s* s) {
     return (s->certified && s->fmt == HYB_SDF_F32) ? hyb::certified_slack(s->grid4[3], s->n) : __builtin_inff();
-}
-
-// The bounds of compute_lipschitz (and check_finite for the compact formats,
-// on the input before it is quantized) left on the device for the kernels,
-// without waiting: the quantization runs between the two passes.
-inline hyb_status deferred_bounds(hyb_sdf_s* s, hipStream_t stream) {
-    const int32_t nb = hyb::lipschitz_blocks(s->n);
-    if (!s->blocks) HYB_TRY(hipMalloc(&s->blocks, sizeof(float) * hyb::kBoundValues * nb));
-    int32_t got = 0;
-    if (s->fmt != HYB_SDF_F32) {
-        HYB_TRY(hyb::launch_lipschitz(s->values, s->n, s->grid4[3], s->blocks, &got, stream));
-        HYB_TRY(hyb::launch_finish_bounds(s->blocks, got, 0, 0.0f, s->dev_bounds, stream));
-    }
-    HYB_TRY(hyb::launch_quantize(s->layout, s->values, s->n, s->store, s->scales, stream));
-    HYB_TRY(hyb::launch_lipschitz(s->values, s->n, s->grid4[3], s->blocks, &got, stream));
-    HYB_TRY(hyb::launch_finish_bounds(s->blocks, got, s->fmt != HYB_SDF_F32 ? 1 : 2, two_e_of(s), s->dev_bounds,
-                                      stream));
-    s->deferred = true;
-    ++s->version;
-    return HYB_OK;
 }
 
 // Allocates the kernels' copy of the samples; *bytes receives its size.
@@ -156,11 +92,27 @@ inline hyb_status allocate_store(hyb_sdf_s* s, size_t* bytes) {
     return HYB_OK;
 }
 
-// Writes the kernels' copy of the FP32 samples in s->values (storage format,
-// bricked layout); for the compact formats the dequantized values replace
-// s->values in place.
-inline hyb_status quantize(hyb_sdf_s* s, hipStream_t stream) {
-    return from_hip(hyb::launch_quantize(s->layout, s->values, s->n, s->store, s->scales, stream));
+// Stores the samples `in` (launch_store) with their step bounds.  Deferred, the
+// bounds stay on the device; else this waits for them, and a sample that is not
+// finite (or an F16 overflow) is an error.
+inline hyb_status store_samples(hyb_sdf_s* s, const float* in, bool deferred, hipStream_t stream) {
+    if (!s->blocks) HYB_TRY(hipMalloc(&s->blocks, sizeof(float) * hyb::kBoundValues * hyb::store_blocks(s->n)));
+    if (!s->dev_bounds) HYB_TRY(hipMalloc(&s->dev_bounds, sizeof(float) * hyb::kDeviceBounds));
+    HYB_TRY(hyb::launch_store(s->layout, in, s->n, s->grid4[3], s->values, s->store, s->scales, s->blocks, two_e_of(s),
+                              s->dev_bounds, stream));
+    if (!deferred) {
+        float b[hyb::kDeviceBounds];
+        HYB_TRY(hipMemcpyAsync(b, s->dev_bounds, sizeof(b), hipMemcpyDeviceToHost, stream));
+        HYB_TRY(hipStreamSynchronize(stream));
+        if (b[hyb::kBBad] != 0.0f) return HYB_ERR_INVALID_ARG;
+        s->lipschitz = b[hyb::kBLipschitz];
+        s->slope[0] = b[hyb::kBSlopeX];
+        s->slope[1] = b[hyb::kBSlopeY];
+        s->slope[2] = b[hyb::kBSlopeZ];
+    }
+    s->deferred = deferred;
+    ++s->version;
+    return HYB_OK;
 }
 
 inline bool valid_fmt(hyb_sdf_format f) { return f == HYB_SDF_F32 || f == HYB_SDF_F16 || f == HYB_SDF_I8_BRICK; }

@@ -1071,12 +1071,15 @@ HYB_HD void cell_slopes(const float f[8], float inv_h, float m[3]) {
     m[2] = fmaxf(fmaxf(fabsf(f[4] - f[0]), fabsf(f[5] - f[1])), fmaxf(fabsf(f[6] - f[2]), fabsf(f[7] - f[3]))) * inv_h;
 }
 
-HYB_HD float cell_lipschitz(const float f[8], float inv_h) {
+// Square of the cell's gradient bound, but for 1 / h^2.
+HYB_HD float cell_gradient2(const float f[8]) {
     const float mx = fmaxf(fmaxf(fabsf(f[1] - f[0]), fabsf(f[3] - f[2])), fmaxf(fabsf(f[5] - f[4]), fabsf(f[7] - f[6])));
     const float my = fmaxf(fmaxf(fabsf(f[2] - f[0]), fabsf(f[3] - f[1])), fmaxf(fabsf(f[6] - f[4]), fabsf(f[7] - f[5])));
     const float mz = fmaxf(fmaxf(fabsf(f[4] - f[0]), fabsf(f[5] - f[1])), fmaxf(fabsf(f[6] - f[2]), fabsf(f[7] - f[3])));
-    return sqrtf(mx * mx + my * my + mz * mz) * inv_h;
+    return mx * mx + my * my + mz * mz;
 }
+
+HYB_HD float cell_lipschitz(const float f[8], float inv_h) { return sqrtf(cell_gradient2(f)) * inv_h; }
 
 // Lipschitz bound used for steps, from the largest cell bound of the grid: at
 // least 1 (keeps steps finite on flat fields), rounded up a few ulps so it

@@ -37,7 +37,7 @@ struct TraceArgs {
     double inv_hd;  // 1 / h in FP64 (scales the distance field's FP64 ray position)
     // Step bounds on the device (null: the fields above hold them): the grid
     // was last updated without a wait (kDeviceBounds floats, see
-    // launch_finish_bounds)
+    // launch_store)
     const float* bounds;
 };
 
@@ -70,9 +70,17 @@ hipError_t launch_count_mismatch(const float* t, const int32_t* prim, const floa
                                  const float* dx, const float* dy, const float* dz, int64_t n, float h,
                                  unsigned long long* count, hipStream_t stream);
 
-// The kernels' copy of an n^3 FP32 grid (x fastest): `out` receives
-// brick_storage(fmt, n) samples in the format's bricked layout (slot s holds
-// the node Brick<fmt>::slot_node(s)), in the storage format:
+constexpr int kBoundValues = 5;
+// Step bounds that the kernels may read on the device: inv_l, slope_x, slope_y,
+// slope_z, two_e, a flag (nonzero: a sample was not finite) and the Lipschitz
+// bound itself.
+constexpr int kDeviceBounds = 8;
+enum DeviceBound : int { kBInvL = 0, kBSlopeX = 1, kBSlopeY = 2, kBSlopeZ = 3, kBTwoE = 4, kBBad = 5, kBLipschitz = 6 };
+
+// Everything that is stored of an n^3 FP32 grid `in` (x fastest): `out` receives
+// the kernels' copy, brick_storage(fmt, n) samples in the format's bricked
+// layout (slot s holds the node Brick<fmt>::slot_node(s)), in the storage
+// format:
 //   F32: the value
 //   F16: round-to-nearest-even half of the value
 //   I8:  scales[b] = the smallest power of two 2^e (e >= -126) with
@@ -81,9 +89,13 @@ hipError_t launch_count_mismatch(const float* t, const int32_t* prim, const floa
 //        q = rint(value / S) clamped to +-floor(127 * smallest / S), an integer
 //        multiple of every holding block's scale; each cell stores the codes of
 //        its 8 corners for its own block's scale, then that scale
-// For F16 / I8, `values` is then overwritten in place by the dequantized FP32
-// values (what the trace kernels interpolate).
-hipError_t launch_quantize(int fmt, float* values, int32_t n, void* out, float* scales, hipStream_t stream);
+// `values` (which may be `in`) receives the samples as the trace kernels
+// interpolate them, and `bounds` (kDeviceBounds floats) the step bounds of
+// those, with two_e the certified-grid slack, or +inf.  block_max: room for
+// kBoundValues floats per block, store_blocks(n) blocks.
+hipError_t launch_store(int fmt, const float* in, int32_t n, float h, float* values, void* out, float* scales,
+                        float* block_max, float two_e, float* bounds, hipStream_t stream);
+int32_t store_blocks(int32_t n);
 
 // Scatter of d loss / d grid sample for distance-field hits (hyb_df_backward):
 // the rays are sorted by hit cell in `workspace` (device memory of at least
@@ -121,27 +133,5 @@ struct SdfBuildArgs {
 // sdf_build_scratch(n_grid) bytes, free again once the work has completed.
 size_t sdf_build_scratch(int32_t n);
 hipError_t launch_sdf_build(const SdfBuildArgs& a, void* scratch, size_t scratch_bytes, hipStream_t stream);
-
-// Per-block maxima of the cell Lipschitz bounds and of the per-axis cell
-// slopes of an n^3 grid (x fastest), and a flag for non-finite samples: block
-// b writes block_max[5 b .. 5 b + 5) = (Lipschitz, slope x, slope y, slope z,
-// 1 if some sample of its cells is NaN or infinite else 0); returns n_blocks
-// through *n_blocks.
-constexpr int kBoundValues = 5;
-// The step bounds a deferred update leaves on the device: inv_l, slope_x,
-// slope_y, slope_z, two_e, a flag (nonzero: a sample was not finite) and the
-// Lipschitz bound itself.
-constexpr int kDeviceBounds = 8;
-enum DeviceBound : int { kBInvL = 0, kBSlopeX = 1, kBSlopeY = 2, kBSlopeZ = 3, kBTwoE = 4, kBBad = 5, kBLipschitz = 6 };
-// Reduces the n_blocks per-block maxima of launch_lipschitz into the step
-// bounds (out, kDeviceBounds floats), as the host does: pass 0 only the
-// non-finite flag (a pass over the input of a compact format, before it is
-// quantized), pass 1 all of them with the flag kept set by pass 0, pass 2 all
-// of them with a fresh flag.  two_e: the certified-grid slack, or +inf.
-hipError_t launch_finish_bounds(const float* block_max, int32_t n_blocks, int pass, float two_e, float* out,
-                                hipStream_t stream);
-hipError_t launch_lipschitz(const float* grid, int32_t n, float h, float* block_max, int32_t* n_blocks,
-                            hipStream_t stream);
-int32_t lipschitz_blocks(int32_t n);
 
 }  // namespace hyb
