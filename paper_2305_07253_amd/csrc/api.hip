@@ -297,6 +297,9 @@ hyb_status hyb_df_backward(hyb_sdf sdf, const hyb_rays* rays, int64_t n, float t
     hyb_hits none = {nullptr, nullptr, nullptr, nullptr};
     fill_trace_args(a, rays, &none, n, tmax, 0.0f);
     fill_scene(a, nullptr, sdf);
+    if (!hyb::df_backward_sorts(n))
+        return from_hip(hyb::launch_df_backward(a, t_hit, grad_t, grad_grid, nullptr, 0,
+                                                static_cast<hipStream_t>(stream)));
     if (n != sdf->bwd_n) {  // sizing the sort costs host time: once per ray count
         sdf->bwd_need = hyb::df_backward_workspace(n, sdf->n);
         sdf->bwd_n = n;

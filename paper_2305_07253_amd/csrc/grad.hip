@@ -3,12 +3,10 @@
 // corners of its hit cell, times grad_t, added into the grid gradient.
 //
 // The float atomic adds are nearly the whole cost of a plain scatter (8 per
-// hit; recomputing the hits is a few percent of it), and the cost is per add.
-// Hits cluster in cells (on a G-buffer-shaped refit several rays end in each
-// touched cell), so the rays are keyed by hit cell and radix-sorted, and each
-// wavefront sums the contributions of consecutive equal keys before the last
-// lane of each run adds them: 8 adds per (wavefront, cell) instead of per
-// ray.
+// hit, 17 to 22 G adds/s, and 4 ns for every add at the same node; recomputing the
+// hits is a few percent of it).  So workgroups sum by node in LDS before they add: up to
+// 2^18 rays in the caller's order, more of them after a radix sort by the block of 8^3
+// cells that they hit, since hits cluster on surfaces.
 #include <rocprim/device/device_radix_sort.hpp>
 
 #include "hyb_device.hpp"
@@ -19,10 +17,10 @@ namespace {
 
 constexpr int kBwdBlock = 256;
 
-// The (cell, ray) pairs are sorted by rocPRIM's onesweep radix sort from 64k
-// pairs up: its default switches to a block sort plus merge passes up to 1M
-// pairs, which took 154 us of a 241 us backward on 1M rays (ten merge
-// passes) where onesweep takes three passes over 22-bit keys.
+// The (block, ray) pairs are sorted by rocPRIM's onesweep radix sort: its default
+// is a block sort plus merge passes up to 1M pairs, which took 154 us of a 241 us
+// backward on 1M rays (ten merge passes) where onesweep takes two passes over the 13
+// bits of a block at 128^3.
 using BwdSortConfig =
     rocprim::radix_sort_config<rocprim::default_config, rocprim::default_config, rocprim::default_config, 65536>;
 
@@ -45,8 +43,36 @@ HYB_HD bool ray_gradient(const TraceArgs& a, const Grid& g, int64_t i, const flo
     return true;
 }
 
-// Sort keys: the hit cell's corner-0 index (below n^3), or `none` (= n^3) for
-// a ray that adds nothing; the values are the ray indices.
+constexpr int kCells = 8;               // cells of a block per axis
+constexpr int kSide = kCells + 1;       // its nodes
+constexpr int kNodes = kSide * kSide * kSide;
+constexpr int kOpen = 8;                // blocks that a workgroup sums at a time
+constexpr int kSparse = 32;             // distinct blocks above which it sums none
+constexpr int kSumBlock = 512;
+constexpr int kSlotBits = 13;
+constexpr int kSlots = 1 << kSlotBits;  // of a workgroup's hash table
+static_assert(kSlots >= 2 * 8 * kSumBlock, "at least half of the table stays empty");
+constexpr uint32_t kEmpty = 0xffffffffu;
+
+// Rays up to which no sort pays: its passes take 50 us and more whatever the count,
+// the unsorted rays' additional global adds take time per ray.  Unsorted against
+// sorted by block: 16k rays on 32^3 12 against 36 us, 128k on 64^3 48 against 85,
+// 256k on 128^3 76 against 101 (32^3 67 against 62, a narrow view 32 against 97), 900k
+// on 160^3 263 against 150, 1M on 128^3 301 against 163.
+constexpr int64_t kUnsorted = 1 << 18;
+
+__host__ __device__ inline int blocks_per_axis(int n) { return (n - 1 + kCells - 1) / kCells; }
+
+// Cell coordinates of a linear node index (below 2^30).
+__device__ void cell_of(int64_t cell, int n, int& i, int& j, int& k) {
+    const uint32_t c = (uint32_t)cell, row = c / (uint32_t)n;
+    i = (int)(c - row * n);
+    k = (int)(row / (uint32_t)n);
+    j = (int)(row - (uint32_t)k * n);
+}
+
+// Sort keys: the hit cell's block, or `none` for a ray that adds nothing; the
+// values are the ray indices.
 __global__ __launch_bounds__(kBwdBlock) void k_bwd_keys(TraceArgs a, const float* __restrict__ t_hit,
                                                         const float* __restrict__ grad_t, uint32_t* __restrict__ keys,
                                                         uint32_t* __restrict__ rays, uint32_t none) {
@@ -55,54 +81,138 @@ __global__ __launch_bounds__(kBwdBlock) void k_bwd_keys(TraceArgs a, const float
     const Grid g = grid_of(a);
     int64_t cell = 0;
     float v[8];
-    keys[i] = ray_gradient(a, g, i, t_hit, grad_t, cell, v) ? (uint32_t)cell : none;
+    uint32_t key = none;
+    if (ray_gradient(a, g, i, t_hit, grad_t, cell, v)) {
+        int ci, cj, ck;
+        cell_of(cell, a.n_grid, ci, cj, ck);
+        const uint32_t nb = blocks_per_axis(a.n_grid);
+        key = ci / kCells + nb * (cj / kCells + nb * (ck / kCells));
+    }
+    keys[i] = key;
     rays[i] = (uint32_t)i;
 }
 
-// Over the sorted keys: each lane recomputes its ray's contributions, the
-// wavefront forms inclusive sums over runs of equal keys (the keys are
-// sorted, so two lanes with equal keys bound a run of them), and the last
-// lane of each run adds the run's sums at the cell's 8 corners.  Every lane
-// of a launched wavefront takes part in the shuffles; lanes past n carry
-// `none`.
-__global__ __launch_bounds__(kBwdBlock) void k_bwd_runs(TraceArgs a, const float* __restrict__ t_hit,
-                                                        const float* __restrict__ grad_t,
-                                                        const uint32_t* __restrict__ keys,
-                                                        const uint32_t* __restrict__ rays,
-                                                        float* __restrict__ grad_grid, uint32_t none) {
-    const int64_t j = (int64_t)blockIdx.x * kBwdBlock + threadIdx.x;
+__device__ void add_corners(float* __restrict__ grad_grid, int64_t cell, int64_t n, const float v[8]) {
+    for (int c = 0; c < 8; ++c)
+        unsafeAtomicAdd(grad_grid + cell + (c & 1) + n * (((c >> 1) & 1) + n * (c >> 2)), v[c]);
+}
+
+// Above kUnsorted rays.  Over the sorted keys, 256 rays per workgroup: each thread
+// recomputes its ray's contributions, the workgroup sums up to kOpen blocks at a time
+// in LDS, a block per table of 9^3 nodes (23 KB: six workgroups per CU; 4 tables and 16
+// the same within 1%, 16 fewer workgroups), and adds what got something.  A workgroup
+// whose rays hit more than kSparse blocks, 8 rays or fewer in each, has little to sum:
+// each ray adds for itself (the line at 64 is the same on grids up to 256^3, where few
+// workgroups are near it).  1M rays on 128^3: keys 14 us, sort 66 us, this 76 us, 164 us
+// with the gaps; sorted by cell, and the runs of equal keys summed in each wavefront
+// (8 global adds for each cell of a wavefront), 193 us.
+__global__ __launch_bounds__(kBwdBlock) void k_bwd_blocks(TraceArgs a, const float* __restrict__ t_hit,
+                                                          const float* __restrict__ grad_t,
+                                                          const uint32_t* __restrict__ keys,
+                                                          const uint32_t* __restrict__ rays,
+                                                          float* __restrict__ grad_grid, uint32_t none) {
+    __shared__ float acc[kOpen * kNodes];
+    __shared__ uint32_t s_block[kBwdBlock];  // the distinct blocks, in order
+    __shared__ int s_heads[kBwdBlock / 64];
+    const int t = threadIdx.x, n = a.n_grid, nb = blocks_per_axis(n), wave = t / 64;
+    const int64_t j = (int64_t)blockIdx.x * kBwdBlock + t;
     const uint32_t key = j < a.n ? keys[j] : none;
-    float v[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    if (key != none) {
-        const Grid g = grid_of(a);
-        int64_t cell = 0;
-        // the same computation as for the key: it succeeds again; the corners
-        // the run adds at come from the key alone
-        if (!ray_gradient(a, g, rays[j], t_hit, grad_t, cell, v))
-            for (int c = 0; c < 8; ++c) v[c] = 0.0f;
+    const uint32_t last = t > 0 && j - 1 < a.n ? keys[j - 1] : none;
+    const bool head = key != none && (t == 0 || key != last);
+    const uint64_t heads = __ballot(head);
+    if (t % 64 == 0) s_heads[wave] = __popcll(heads);
+    for (int q = t; q < kOpen * kNodes; q += kBwdBlock) acc[q] = 0.0f;
+    float v[8];
+    int ci = 0, cj = 0, ck = 0;
+    int64_t cell = 0;
+    // the same computation as for the key: it succeeds again
+    const bool found = key != none && ray_gradient(a, grid_of(a), rays[j], t_hit, grad_t, cell, v);
+    if (found) cell_of(cell, n, ci, cj, ck);
+    __syncthreads();
+    int before = 0, total = 0;
+    for (int w = 0; w < kBwdBlock / 64; ++w) {
+        if (w < wave) before += s_heads[w];
+        total += s_heads[w];
     }
-    // every shuffle runs on all 64 lanes (a lane reads its source's value
-    // only while the source is active), so none sits behind a condition
-    const int lane = threadIdx.x & 63;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t up = __shfl_up(key, o);
-        const bool same = lane >= o && up == key;
-        for (int c = 0; c < 8; ++c) {
-            const float w = __shfl_up(v[c], o);
-            if (same) v[c] += w;
+    // this ray's block among the workgroup's (the keys are sorted)
+    const int mine = before + __popcll(heads & (~uint64_t(0) >> (63 - t % 64))) - 1;
+    if (total > kSparse) {
+        if (found) add_corners(grad_grid, cell, n, v);
+        return;
+    }
+    if (head) s_block[mine] = key;
+    for (int base = 0; base < total; base += kOpen) {
+        __syncthreads();  // s_block written; the tables cleared
+        if (found && mine >= base && mine < base + kOpen) {
+            const int i = ci - (int)(key % nb) * kCells, jj = cj - (int)(key / nb % nb) * kCells,
+                      k = ck - (int)(key / nb / nb) * kCells;
+            if ((unsigned)i < kCells && (unsigned)jj < kCells && (unsigned)k < kCells) {
+                float* p = acc + (mine - base) * kNodes + i + kSide * (jj + kSide * k);
+                for (int c = 0; c < 8; ++c) atomicAdd(p + (c & 1) + kSide * (((c >> 1) & 1) + kSide * (c >> 2)), v[c]);
+            } else {  // a recomputation that rounded to another block than the key's
+                add_corners(grad_grid, cell, n, v);
+            }
         }
-    }
-    const uint32_t next = __shfl_down(key, 1);
-    const bool last = lane == 63 || next != key;
-    if (key == none || !last) return;
-    const int64_t n = a.n_grid;
-    for (int c = 0; c < 8; ++c) {
-        const int64_t node = (int64_t)key + (c & 1) + n * (((c >> 1) & 1) + n * (c >> 2));
-        unsafeAtomicAdd(grad_grid + node, v[c]);
+        __syncthreads();
+        const int open = min(kOpen, total - base);
+        for (int q = t; q < open * kNodes; q += kBwdBlock) {
+            const float sum = acc[q];
+            if (sum == 0.0f) continue;  // a node that no ray touched, or beyond the grid
+            acc[q] = 0.0f;
+            const uint32_t block = s_block[base + q / kNodes];
+            const int r = q % kNodes;
+            const int i = (int)(block % nb) * kCells + r % kSide, jj = (int)(block / nb % nb) * kCells + r / kSide % kSide,
+                      k = (int)(block / nb / nb) * kCells + r / (kSide * kSide);
+            unsafeAtomicAdd(grad_grid + i + (int64_t)n * (jj + (int64_t)n * k), sum);
+        }
     }
 }
 
-uint32_t key_none(int32_t n_grid) { return (uint32_t)((int64_t)n_grid * n_grid * n_grid); }
+// Up to kUnsorted rays: one launch over the rays in the caller's order, each
+// workgroup's 512 rays summed by node in a hash table in LDS (linear probing; at most
+// 8 * 512 of its 8,192 slots are taken, so that every probe ends) before the nodes are
+// added.  Neighbouring rays of an image share nodes, and what narrow views or small
+// grids need is that few workgroups add at one node: 64k rays into about 20 cells take
+// 15 us so and 280 us when each wavefront sums its own.  64 KB: two workgroups per CU.
+__global__ __launch_bounds__(kSumBlock) void k_bwd_sum(TraceArgs a, const float* __restrict__ t_hit,
+                                                       const float* __restrict__ grad_t,
+                                                       float* __restrict__ grad_grid) {
+    __shared__ uint32_t s_node[kSlots];
+    __shared__ float s_sum[kSlots];
+    const int64_t i = (int64_t)blockIdx.x * kSumBlock + threadIdx.x;
+    for (int q = threadIdx.x; q < kSlots; q += kSumBlock) {
+        s_node[q] = kEmpty;
+        s_sum[q] = 0.0f;
+    }
+    int64_t cell = 0;
+    float v[8];
+    const bool found = i < a.n && ray_gradient(a, grid_of(a), i, t_hit, grad_t, cell, v);
+    __syncthreads();
+    if (found) {
+        const uint32_t n = (uint32_t)a.n_grid;
+        uint32_t node[8], slot[8], old[8];
+        for (int c = 0; c < 8; ++c) {
+            node[c] = (uint32_t)cell + (c & 1) + n * (((c >> 1) & 1) + n * (c >> 2));
+            slot[c] = (node[c] * 2654435769u) >> (32 - kSlotBits);
+            old[c] = atomicCAS(&s_node[slot[c]], kEmpty, node[c]);
+        }
+        for (int c = 0; c < 8; ++c) {
+            while (old[c] != kEmpty && old[c] != node[c]) {
+                slot[c] = (slot[c] + 1) % kSlots;
+                old[c] = atomicCAS(&s_node[slot[c]], kEmpty, node[c]);
+            }
+            atomicAdd(&s_sum[slot[c]], v[c]);
+        }
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < kSlots; q += kSumBlock)
+        if (s_node[q] != kEmpty) unsafeAtomicAdd(grad_grid + s_node[q], s_sum[q]);
+}
+
+uint32_t key_none(int32_t n_grid) {
+    const uint32_t nb = blocks_per_axis(n_grid);
+    return nb * nb * nb;
+}
 
 int key_bits(int32_t n_grid) {
     const uint32_t none = key_none(n_grid);
@@ -121,6 +231,8 @@ size_t sort_temp_bytes(int64_t n, int32_t n_grid) {
 
 }  // namespace
 
+bool df_backward_sorts(int64_t n) { return n > kUnsorted; }
+
 size_t df_backward_workspace(int64_t n, int32_t n_grid) {
     if (n <= 0) return 0;
     const size_t t = sort_temp_bytes(n, n_grid);
@@ -131,6 +243,11 @@ size_t df_backward_workspace(int64_t n, int32_t n_grid) {
 hipError_t launch_df_backward(const TraceArgs& a, const float* t_hit, const float* grad_t, float* grad_grid,
                               void* workspace, size_t workspace_bytes, hipStream_t stream) {
     if (a.n <= 0) return hipSuccess;
+    if (!df_backward_sorts(a.n)) {
+        hipLaunchKernelGGL(k_bwd_sum, dim3((unsigned)((a.n + kSumBlock - 1) / kSumBlock)), dim3(kSumBlock), 0, stream,
+                           a, t_hit, grad_t, grad_grid);
+        return hipGetLastError();
+    }
     // four arrays of n words (keys and ray indices, each twice for the sort's
     // passes), then the sort's scratch: the caller sized it with
     // df_backward_workspace(a.n, a.n_grid)
@@ -150,8 +267,7 @@ hipError_t launch_df_backward(const TraceArgs& a, const float* t_hit, const floa
     e = rocprim::radix_sort_pairs<BwdSortConfig>(p + 4 * arr, temp_bytes, keys, rays, static_cast<int>(a.n), 0,
                                                  key_bits(a.n_grid), stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bwd_runs, dim3(blocks), dim3(kBwdBlock), 0, stream, a, t_hit, grad_t, keys.current(),
-                       rays.current(), grad_grid, none);
+    hipLaunchKernelGGL(k_bwd_blocks, dim3(blocks), dim3(kBwdBlock), 0, stream, a, t_hit, grad_t, keys.current(), rays.current(), grad_grid, none);
     return hipGetLastError();
 }
 

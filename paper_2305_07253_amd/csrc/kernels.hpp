@@ -98,9 +98,10 @@ hipError_t launch_store(int fmt, const float* in, int32_t n, float h, float* val
 int32_t store_blocks(int32_t n);
 
 // Scatter of d loss / d grid sample for distance-field hits (hyb_df_backward):
-// the rays are sorted by hit cell in `workspace` (device memory of at least
-// df_backward_workspace(a.n, a.n_grid) bytes, which is 0 when the sort cannot
-// be sized), and each wavefront adds once per cell.
+// where df_backward_sorts(a.n), the rays are sorted by the block of cells they hit
+// in `workspace` (device memory of at least df_backward_workspace(a.n, a.n_grid)
+// bytes, which is 0 when the sort cannot be sized); otherwise it is not used.
+bool df_backward_sorts(int64_t n);
 size_t df_backward_workspace(int64_t n, int32_t n_grid);
 hipError_t launch_df_backward(const TraceArgs& a, const float* t_hit, const float* grad_t, float* grad_grid,
                               void* workspace, size_t workspace_bytes, hipStream_t stream);
