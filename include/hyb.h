@@ -318,9 +318,9 @@ hyb_status hyb_sdf_destroy(hyb_sdf sdf);
  *
  * Each item is an independent combined query (as hyb_trace) of its own scene
  * with its own threshold; a batch runs all of them in one persistent kernel
- * whose wavefronts take runs of rays_per_item rays of one item from a global
- * work counter until every item is done.  hyb_batch_launch replays a HIP graph
- * of two kernel nodes (a fill kernel that zeroes the counter, then the
+ * whose wavefronts take runs of at most rays_per_item rays of one item from
+ * work counters until every item is done.  hyb_batch_launch replays a HIP graph
+ * of two kernel nodes (a fill kernel that zeroes the counters, then the
  * persistent trace); hyb_batch_launch_eager launches the same two kernels
  * directly.  Results are bit-identical to hyb_trace per item, whatever the
  * launch configuration.
@@ -347,7 +347,8 @@ typedef struct {
 /* Launch shape of the persistent kernel. */
 typedef struct {
     int32_t lds_depth;      /* BVH stack entries per lane held in LDS: 8, 16 or 32 (rest spills) */
-    int32_t rays_per_item;  /* rays per work item, multiple of 64 in [64, 65536] */
+    int32_t rays_per_item;  /* most rays per work item, multiple of 64 in [64, 65536] (fewer are
+                               taken where they fill the chip better) */
     int32_t blocks_per_cu;  /* 256-thread blocks per compute unit, 1..16 (capped by occupancy) */
 } hyb_batch_config;
 
@@ -418,7 +419,7 @@ hyb_status hyb_batch_destroy(hyb_batch batch);
  * launch of the same items and config.
  *   config  launch shape, or NULL for the default {16, 256, 4}
  * Every call on a device shares that device's array and leaves its contents
- * behind (each call rewrites what it uses and zeroes the counter itself):
+ * behind (each call rewrites what it uses and zeroes the counters itself):
  * calls that overlap on one device (other streams, other threads) race.
  * Errors: HYB_ERR_INVALID_ARG for NULL items, n_items < 1 or n_items >
  * HYB_STATIC_BATCH_MAX_ITEMS, a bad config, or an item hyb_batch_create would

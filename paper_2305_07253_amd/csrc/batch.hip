@@ -5,8 +5,8 @@
 //
 // The combined query itself (Section 2, Eq. (2)) is the same per-ray code as
 // hyb_trace; only the mapping of rays to wavefronts differs.  Every wavefront
-// takes work items (a run of rays_per_item consecutive rays of one scene) from
-// a device counter until the counter passes the last item, so scenes of very
+// takes work items (a run of consecutive rays of one scene) from one of eight
+// device counters until the counter passes its last item, so scenes of very
 // different sizes share the chip without a tail per scene.
 #include <hip/hip_runtime.h>
 
@@ -26,33 +26,49 @@ namespace {
 
 constexpr int kWave = 64;
 
-// FP32: six wavefronts per SIMD (at most 80 VGPRs); left to itself the
-// compiler takes 83 registers and runs five, 6% slower on the 64-scene batch.
-// The compact formats would spill at six and keep five.
+// Work counters, 32 bytes apart in the 256 of a handle or the static array.
+constexpr int kQueueStride = 8;
+
+// Bound by the latency of its wavefronts (four per SIMD in the default configuration)
+// and by the last of them.  Held to five wavefronts per SIMD: at six, 80 VGPRs, FP32 takes
+// 407 us for 12 scenes with 1.7M rays instead of 374 (at six blocks per CU 347 instead of
+// 342), at seven 508; left alone F16 takes 99 registers and loses the fifth.
+//
+// Blocks share a counter with those of their die (the dispatcher hands block b to die
+// b mod kXcds): counters that eight dies add to serve a pop in 17 ns, which at items of
+// 64 rays was the bound with many wavefronts (one counter 447 us at four blocks per CU
+// and 459 at six, eight counters 406 and 349).  Each counter hands out every eighth
+// item, so no die runs out early; consecutive runs of 8 to 64 items took the same time.
 template <int FMT, int LDS>
-__global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(FMT == kF32 ? 6 : 5))) void k_trace_batch(
+__global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_trace_batch(
     BatchArgs b, const TraceArgs* __restrict__ scenes) {
     extern __shared__ int s_stack[];
     const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t queues = min((uint32_t)kXcds, gridDim.x), queue = blockIdx.x % queues;
     for (;;) {
-        uint32_t w = 0;
-        if (lane == 0) w = atomicAdd(b.queue, 1u);
-        w = __builtin_amdgcn_readfirstlane(__shfl(w, 0, kWave));
-        if (w >= b.n_items) return;  // every wavefront ends here once the queue has passed n_items
-        // scene s with item_start[s] <= w < item_start[s + 1] (empty scenes own no item)
-        int lo = 0, hi = b.n_scenes;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (b.item_start[mid] <= w) lo = mid;
-            else hi = mid;
+        uint32_t k = 0;
+        if (lane == 0) k = atomicAdd(b.queue + kQueueStride * queue, 1u);
+        k = __builtin_amdgcn_readfirstlane(k);
+        const uint32_t w = k * queues + queue;
+        if (w >= b.n_items) return;  // every wavefront ends here once its counter has passed its items
+        // scene s with item_start[s] <= w < item_start[s + 1] (empty scenes own no
+        // item): each step splits the range in 64
+        int lo = 0, size = b.n_scenes;
+        while (size > 1) {
+            const int step = (size + kWave - 1) / kWave, at = lo + lane * step;
+            const uint64_t below = __ballot(lane * step < size && b.item_start[at] <= w);
+            const int part = __popcll(below) - 1;
+            size = min(step, size - part * step);
+            lo += part * step;
         }
         // The scene's arguments are the same for the whole wavefront (lo is
         // uniform) and the table is never written by the kernel: its fields
         // are read with scalar loads where they are used.
         const TraceArgs& a = scenes[__builtin_amdgcn_readfirstlane(lo)];
-        const int64_t base = (int64_t)(w - b.item_start[lo]) * b.rays_per_item;
-        for (int k = 0; k < b.rays_per_item; k += kWave) {
-            const int64_t i = base + k + lane;
+        // (an item of fewer than 64 rays: several lanes trace each, all alike)
+        const int64_t base = (int64_t)(w - b.item_start[lo]) * b.rays_per_item + (lane & (b.rays_per_item - 1) & 63);
+        for (int first = 0; first < b.rays_per_item; first += kWave) {
+            const int64_t i = base + first;
             if (i >= a.n) continue;
             // F16 scenes may differ in brick layout (a.fmt is the same for
             // the whole wavefront)
@@ -65,7 +81,7 @@ __global__ __launch_bounds__(kBatchBlock) __attribute__((amdgpu_waves_per_eu(FMT
 }
 
 __global__ void k_queue_reset(uint32_t* counter) {
-    if (threadIdx.x == 0) counter[0] = 0u;
+    if (threadIdx.x < kXcds) counter[kQueueStride * threadIdx.x] = 0u;
 }
 
 __global__ __launch_bounds__(kBatchBlock) void k_count_mismatch(const float* __restrict__ t, const int32_t* __restrict__ prim,
@@ -270,6 +286,33 @@ void item_args(const hyb_batch_item& it, hyb::TraceArgs& a) {
     if (!it.sdf) a.h = 1.0f;  // t1 = fma(+inf, h, tmin) must be +inf (then min(., tmax) = tmax), not NaN
 }
 
+// Rays per work item: those of one wavefront, whatever the configuration's upper limit
+// (64 against 256 rays: 12 scenes with 1.7M rays 374 and 474 us, 96 scenes with 14M
+// 2,510 and 2,591, one of 13,376 76 and 214), and fewer in a batch that leaves most of the chip
+// idle (rays_shift).  Longer ones keep a batch's items below 2^20 where the
+// configuration allows, below the limit of their number in any case.
+int32_t item_rays(const hyb_batch_config& cfg, uint64_t rays) {
+    uint32_t shift = hyb::rays_shift(hyb::kCombined, static_cast<int64_t>(std::min<uint64_t>(rays, 1u << 30)));
+    while ((1u << shift) < static_cast<uint32_t>(cfg.rays_per_item) && rays >> shift > (1u << 20)) ++shift;
+    return std::min(1 << shift, cfg.rays_per_item);
+}
+
+// The items of a batch (n_items of them, item i with rays(i) rays): rays per item in
+// *item, and where each one's items start.
+template <class Rays>
+hyb_status place_items(const hyb_batch_config& cfg, int32_t n_items, const Rays& rays, uint32_t* start, int32_t* item) {
+    uint64_t n = 0, total = 0;
+    for (int32_t s = 0; s < n_items; ++s) n += static_cast<uint64_t>(rays(s));
+    *item = item_rays(cfg, n);
+    for (int32_t s = 0; s < n_items; ++s) {
+        start[s] = static_cast<uint32_t>(total);
+        total += (static_cast<uint64_t>(rays(s)) + *item - 1) / *item;
+        if (total >= kMaxWorkItems) return HYB_ERR_UNSUPPORTED;
+    }
+    start[n_items] = static_cast<uint32_t>(total);
+    return HYB_OK;
+}
+
 // Blocks of the persistent launch: as many as the GPU holds at the config's
 // blocks per CU (capped by occupancy), never more than the work needs.
 hyb_status persistent_grid(int fmt, const hyb_batch_config& cfg, int n_cu, uint64_t work_items, dim3* grid) {
@@ -278,8 +321,9 @@ hyb_status persistent_grid(int fmt, const hyb_batch_config& cfg, int n_cu, uint6
     int occ = 0;
     HYB_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, hyb::kBatchBlock, hyb::batch_lds_bytes(cfg.lds_depth)));
     const int64_t per_cu = std::max(1, std::min(occ, cfg.blocks_per_cu));
-    const int64_t waves_needed = (static_cast<int64_t>(work_items) + 3) / 4;  // 4 wavefronts per block
-    *grid = dim3(static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(per_cu * n_cu, waves_needed))));
+    // 4 wavefronts per block, as many blocks on each die's counter
+    const int64_t blocks_needed = (static_cast<int64_t>(work_items) + 4 * hyb::kXcds - 1) / (4 * hyb::kXcds) * hyb::kXcds;
+    *grid = dim3(static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(per_cu * n_cu, blocks_needed))));
     return HYB_OK;
 }
 
@@ -310,13 +354,11 @@ hyb_status sync_table(hyb_batch_s* b, hipStream_t stream) {
     refresh_grids(b);
     if (!b->table_dirty) return HYB_OK;
     const int32_t n_scenes = static_cast<int32_t>(b->args.size());
-    uint64_t total = 0;
-    for (int32_t s = 0; s < n_scenes; ++s) {
-        b->item_start[s] = static_cast<uint32_t>(total);
-        total += (static_cast<uint64_t>(b->args[s].n) + b->cfg.rays_per_item - 1) / b->cfg.rays_per_item;
-        if (total >= kMaxWorkItems) return HYB_ERR_UNSUPPORTED;
-    }
-    b->item_start[n_scenes] = static_cast<uint32_t>(total);
+    int32_t item = 0;
+    const hyb_status placed =
+        place_items(b->cfg, n_scenes, [&](int32_t s) { return b->args[s].n; }, b->item_start.data(), &item);
+    if (placed != HYB_OK) return placed;
+    const uint32_t total = b->item_start[n_scenes];
     HYB_TRY(hipMemcpyAsync(b->d_args, b->args.data(), sizeof(hyb::TraceArgs) * n_scenes, hipMemcpyHostToDevice, stream));
     HYB_TRY(hipMemcpyAsync(b->d_item_start, b->item_start.data(), sizeof(uint32_t) * (n_scenes + 1),
                            hipMemcpyHostToDevice, stream));
@@ -329,14 +371,14 @@ hyb_status sync_table(hyb_batch_s* b, hipStream_t stream) {
     // The graph's kernel nodes hold the launch shape and BatchArgs by value;
     // a change of thresholds alone only rewrites the device table.
     const bool same_shape = b->grid.x == static_cast<unsigned>(blocks) && b->kargs.n_items == total &&
-                            b->kargs.rays_per_item == b->cfg.rays_per_item && b->graph_lds == b->cfg.lds_depth;
+                            b->kargs.rays_per_item == item && b->graph_lds == b->cfg.lds_depth;
     b->grid = dim3(static_cast<unsigned>(blocks));
     b->kargs.scenes = b->d_args;
     b->kargs.item_start = b->d_item_start;
     b->kargs.queue = b->d_queue;
     b->kargs.n_scenes = n_scenes;
     b->kargs.n_items = static_cast<uint32_t>(total);
-    b->kargs.rays_per_item = b->cfg.rays_per_item;
+    b->kargs.rays_per_item = item;
     b->table_dirty = false;
     if (!same_shape) drop_graph(b);
     b->graph_lds = b->cfg.lds_depth;
@@ -638,13 +680,10 @@ hyb_status hyb_batch_launch_static(const hyb_batch_item* items, int32_t n_items,
     // offsets and descriptors on the stack: nothing is allocated, on the
     // device or the host
     uint32_t item_start[HYB_STATIC_BATCH_MAX_ITEMS + 1];
-    uint64_t total = 0;
-    for (int32_t s = 0; s < n_items; ++s) {
-        item_start[s] = static_cast<uint32_t>(total);
-        total += (static_cast<uint64_t>(items[s].n) + cfg.rays_per_item - 1) / cfg.rays_per_item;
-        if (total >= kMaxWorkItems) return HYB_ERR_UNSUPPORTED;
-    }
-    item_start[n_items] = static_cast<uint32_t>(total);
+    int32_t item = 0;
+    const hyb_status placed = place_items(cfg, n_items, [&](int32_t s) { return items[s].n; }, item_start, &item);
+    if (placed != HYB_OK) return placed;
+    const uint32_t total = item_start[n_items];
     dim3 grid;
     const hyb_status gs = persistent_grid(fmt, cfg, n_cu, total, &grid);
     if (gs != HYB_OK) return gs;
@@ -670,7 +709,7 @@ hyb_status hyb_batch_launch_static(const hyb_batch_item* items, int32_t n_items,
     kargs.queue = queue;
     kargs.n_scenes = n_items;
     kargs.n_items = static_cast<uint32_t>(total);
-    kargs.rays_per_item = cfg.rays_per_item;
+    kargs.rays_per_item = item;
     void* trace_args[] = {&kargs, &scenes};
     return from_hip(hipLaunchKernel(hyb::batch_kernel(fmt, cfg.lds_depth), grid, dim3(hyb::kBatchBlock), trace_args,
                                     hyb::batch_lds_bytes(cfg.lds_depth), st));

@@ -41,19 +41,21 @@ struct TraceArgs {
     const float* bounds;
 };
 
+// Rays of a wavefront (2^shift) of a launch over n rays.
+uint32_t rays_shift(int mode, int64_t n);
 hipError_t launch_trace(int mode, bool counters, const TraceArgs& a, hipStream_t stream);
 
 // Persistent multi-scene trace (combined query of every scene).  Work item w
 // covers rays [(w - item_start[s]) * rays_per_item, ...) of the scene s with
-// item_start[s] <= w < item_start[s + 1]; wavefronts take items from the
-// global counter *queue (zero before the launch) until it passes n_items.
+// item_start[s] <= w < item_start[s + 1]; wavefronts take items from eight
+// counters in the 256 bytes at queue (zero before the launch) until they pass n_items.
 struct BatchArgs {
     const TraceArgs* scenes;     // device table, n_scenes entries
     const uint32_t* item_start;  // device, n_scenes + 1 entries, item_start[n_scenes] = n_items
-    uint32_t* queue;             // device counter
+    uint32_t* queue;             // device counters
     int32_t n_scenes;
     uint32_t n_items;
-    int32_t rays_per_item;       // multiple of 64
+    int32_t rays_per_item;       // a power of two up to 64, or a multiple of 64
 };
 
 // Kernel entry of the persistent trace for a storage format and LDS stack

@@ -24,7 +24,7 @@ namespace hyb {
 // for 113 us.  The distance field alone diverges less: to 1,024 wavefronts and
 // 8,192 rays (1,000 rays 29 -> 25 us, 4,096 34 -> 27 us), 16,384 rays took 3 to
 // 5% longer.
-static uint32_t rays_shift(int mode, int64_t n) {
+uint32_t rays_shift(int mode, int64_t n) {
     if (mode == kDfOnly && n > 8192) return 6;
     const int64_t waves = mode == kDfOnly ? 1024 : 2048;
     uint32_t shift = 0;
