@@ -134,8 +134,8 @@ typedef struct {
  *   verts  host, n_verts x 3 floats (x,y,z)
  *   tris   host, n_tris x 3 int32 vertex indices; 0 <= index < n_verts
  * n_tris == 0 is allowed (every ray misses).  Degenerate triangles are kept and
- * are never hit.  The tree is a binned-SAH binary BVH (used by hyb_build_sdf)
- * collapsed to four children per node for the trace kernels.  Errors: NULL
+ * are never hit.  The tree is a binned-SAH binary BVH
+ * collapsed to four children per node.  Errors: NULL
  * pointers with nonzero counts, negative counts, out-of-range indices or
  * non-finite vertices -> HYB_ERR_INVALID_ARG; a tree deeper than 64 levels or
  * whose traversal could need more than 96 stack entries ->

@@ -1,9 +1,8 @@
 // Binned-SAH BVH2 construction on the host (Wald, "On fast construction of
 // SAH-based bounding volume hierarchies", 2007: 32 bins per axis over the
-// centroid bounds), flattened into 64-byte two-child nodes (read by the
-// distance-field build's nearest-triangle queries), collapsed into 128-byte
-// four-wide nodes that the trace traversal reads with seven 16-byte loads, and
-// the pyramid of traversal entry points.
+// centroid bounds), flattened into 64-byte two-child nodes (which stay on the
+// host), collapsed into 128-byte four-wide nodes that the traversals read with
+// 16-byte loads, and the placement of the pyramid of traversal entry points.
 #include "bvh_build.hpp"
 
 #include <algorithm>
