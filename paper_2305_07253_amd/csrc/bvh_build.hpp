@@ -12,6 +12,9 @@ namespace hyb {
 constexpr int kLeafMax = 4;
 constexpr int kMaxDepth = 64;
 constexpr int kStackDepth4 = 96;  // traversal stack entries per lane for nodes4
+// The same for a traversal that pushes every child it hits and then takes one: it holds
+// that one too for a moment, also where the others fill the stack.
+constexpr int kStackAll4 = kStackDepth4 + 1;
 constexpr int32_t kEmptyRef = ~0;  // a leaf with no triangles
 constexpr int kNode4Parent = 28, kNode4Depth = 29;  // floats of a nodes4 node
 constexpr int kTriLeafParent = 7;                   // float of a leaf's first triangle

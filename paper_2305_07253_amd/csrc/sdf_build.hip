@@ -319,7 +319,7 @@ constexpr int kCastBlocks = 8192;
 // this way, on four times the wavefronts (0.42 -> 0.15 ms at 128^3 against one
 // lane per ray).
 __global__ __launch_bounds__(kWave) void k_sdf_cast(SdfBuildArgs a) {
-    __shared__ int s_stack[kCastRays * kStackDepth4];
+    __shared__ int s_stack[kCastRays * kStackAll4];
     const int lane = threadIdx.x, c = lane & 3;
     int* stack = s_stack + (lane >> 2);  // entries kCastRays apart
     const int64_t n = a.n_grid;
