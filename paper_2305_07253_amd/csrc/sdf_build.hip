@@ -68,13 +68,17 @@ __device__ Around around(double p) {
     return {f - e, f + e};
 }
 
-// Squared distance of a point to a box from below, but for a relative rounding
-// error (at most 4e-7) that every use allows for.
+// Squared distance of a point to a box from below, but for a rounding error (relative,
+// at most 4e-7, and 3e-45 of products below the normal range) that every use allows for.
 __device__ float box_below(Around x, Around y, Around z, float lx, float hx, float ly, float hy, float lz, float hz) {
     const float dx = fmaxf(fmaxf(lx - x.hi, x.lo - hx), 0.0f), dy = fmaxf(fmaxf(ly - y.hi, y.lo - hy), 0.0f),
                 dz = fmaxf(fmaxf(lz - z.hi, z.lo - hz), 0.0f);
     return fmaf(dx, dx, fmaf(dy, dy, dz * dz));
 }
+
+// A squared distance in FP32, from above by the error that box_below may have (the
+// constant: of its products below the normal range).
+__device__ float bound_of(double d2) { return fmaf((float)d2, 1.0f + 2e-6f, 1e-43f); }
 
 // Largest value of the wavefront, in every lane (all lanes active).
 __device__ float wave_max(float v) {
@@ -183,14 +187,14 @@ __global__ __launch_bounds__(kWave) void k_sdf_nearest(SdfBuildArgs a, const flo
                     const double t = tri_dist2(p, dvert(v0), dvert(v1), dvert(v2));
                     if (t < best) {
                         best = t;
-                        bound = (float)t * (1.0f + 2e-6f);
+                        bound = bound_of(t);
                         nearer = true;
                     }
                 }
             }
             if (__ballot(nearer) != 0) {
                 const float far = sqrtf(wave_max(bound)) + reach;
-                limit = far * far * (1.0f + 4e-6f);
+                limit = fmaf(far * far, 1.0f + 4e-6f, 1e-43f);
             }
         }
         bool found = false;
