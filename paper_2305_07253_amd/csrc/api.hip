@@ -103,12 +103,12 @@ hyb_status hyb_build_sdf(hyb_bvh bvh, int32_t n, const float* grid4, uint32_t fl
     if (!bvh || n < 8 || n > 1024 || (flags & ~HYB_SDF_EXTERIOR_SOLID) || !valid_fmt(fmt)) return HYB_ERR_INVALID_ARG;
     if (!same_device(bvh->device)) return HYB_ERR_INVALID_ARG;
     float g4[4];
+    float ext = 0.0f;
+    for (int a = 0; a < 3; ++a) ext = std::max(ext, bvh->hi[a] - bvh->lo[a]);
     if (grid4) {
         if (!valid_grid4(grid4)) return HYB_ERR_INVALID_ARG;
         std::memcpy(g4, grid4, sizeof(g4));
     } else {
-        float ext = 0.0f;
-        for (int a = 0; a < 3; ++a) ext = std::max(ext, bvh->hi[a] - bvh->lo[a]);
         g4[3] = ext > 0.0f ? ext / static_cast<float>(n - 5) : 1.0f;
         for (int a = 0; a < 3; ++a) g4[a] = bvh->lo[a] - 2.0f * g4[3];
     }
@@ -128,6 +128,8 @@ hyb_status hyb_build_sdf(hyb_bvh bvh, int32_t n, const float* grid4, uint32_t fl
         hyb::SdfBuildArgs a = {};
         a.nodes4 = bvh->nodes4;
         a.tris = bvh->tris;
+        a.n_tris = bvh->n_tris;
+        a.extent = ext;
         a.boundary = bvh->boundary;
         a.n_grid = n;
         a.lo_x = g4[0];

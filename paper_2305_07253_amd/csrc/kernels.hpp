@@ -120,6 +120,8 @@ hipError_t launch_mesh_boundary(const float4* tris, int64_t n_tris, unsigned lon
 struct SdfBuildArgs {
     const float4* nodes4;
     const float4* tris;
+    int64_t n_tris;
+    float extent;  // of the mesh, the largest of its box's sides
     const unsigned long long* boundary;  // of launch_mesh_boundary
     int32_t n_grid;
     float lo_x, lo_y, lo_z, h;

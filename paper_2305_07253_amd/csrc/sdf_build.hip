@@ -3,7 +3,8 @@
 // sdf_device.hpp), rounded once to FP32.
 //
 //   k_mesh_boundary   (with the tree) is the mesh a closed surface?
-//   k_sdf_nearest     unsigned distances, one wavefront per 4^3 nodes
+//   k_sdf_nearest     unsigned distances, one wavefront per 4^3 nodes, or
+//   k_sdf_nearest_apart  four lanes per node
 //   k_sdf_components  nodes joined across surface-free balls, per 8^3 nodes
 //   k_sdf_cast        the winding number of one node per component
 //   k_sdf_sign        every other node takes its component's sign
@@ -74,6 +75,12 @@ __device__ float box_below(Around x, Around y, Around z, float lx, float hx, flo
     const float dx = fmaxf(fmaxf(lx - x.hi, x.lo - hx), 0.0f), dy = fmaxf(fmaxf(ly - y.hi, y.lo - hy), 0.0f),
                 dz = fmaxf(fmaxf(lz - z.hi, z.lo - hz), 0.0f);
     return fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+}
+
+// The same for a triangle's box.
+__device__ float triangle_below(Around x, Around y, Around z, float4 a, float4 b, float4 c) {
+    return box_below(x, y, z, fminf(fminf(a.x, b.x), c.x), fmaxf(fmaxf(a.x, b.x), c.x), fminf(fminf(a.y, b.y), c.y),
+                     fmaxf(fmaxf(a.y, b.y), c.y), fminf(fminf(a.z, b.z), c.z), fmaxf(fmaxf(a.z, b.z), c.z));
 }
 
 // A squared distance in FP32, from above by the error that box_below may have (the
@@ -180,9 +187,7 @@ __global__ __launch_bounds__(kWave) void k_sdf_nearest(SdfBuildArgs a, const flo
             for (int q = 0; q < count; ++q) {
                 const float4* tp = tris + 3 * (int64_t)(first + q);
                 const float4 v0 = tp[0], v1 = tp[1], v2 = tp[2];
-                const float b = box_below(x, y, z, fminf(fminf(v0.x, v1.x), v2.x), fmaxf(fmaxf(v0.x, v1.x), v2.x),
-                                          fminf(fminf(v0.y, v1.y), v2.y), fmaxf(fmaxf(v0.y, v1.y), v2.y),
-                                          fminf(fminf(v0.z, v1.z), v2.z), fmaxf(fmaxf(v0.z, v1.z), v2.z));
+                const float b = triangle_below(x, y, z, v0, v1, v2);
                 if (b <= bound) {
                     const double t = tri_dist2(p, dvert(v0), dvert(v1), dvert(v2));
                     if (t < best) {
@@ -212,6 +217,83 @@ __global__ __launch_bounds__(kWave) void k_sdf_nearest(SdfBuildArgs a, const flo
     }
     if (blockIdx.x == 0 && lane == 0) *a.count = 0;
     if (i < n && j < n && k < n) out[i + (int64_t)n * (j + (int64_t)n * k)] = (float)sqrt(best);
+}
+
+constexpr int kQuads = kWave / 4;  // nodes or rays of a wavefront that gives four lanes to each
+
+__device__ float quad_min(float v) {
+    v = fminf(v, __shfl_xor(v, 1, kWave));
+    return fminf(v, __shfl_xor(v, 2, kWave));
+}
+
+// The same for nodes that lie far apart beside the triangles (nodes_apart): a traversal
+// for each node, four lanes to a node, one for each child of a tree node and each
+// triangle of a leaf, nearest child first, with the stack in LDS.  The same triangles'
+// distances, so the same result.  Bound by the chain of visits of its longest node,
+// some 300 to 500 of them at half a microsecond: 188,572 triangles at 12^3 take 0.3 ms,
+// field and all, where one thread per node took 0.9 and packets, which visit 4,263 nodes and
+// measure 7,168 triangles in one wavefront, 6.7.
+__global__ __launch_bounds__(kWave) void k_sdf_nearest_apart(SdfBuildArgs a) {
+    __shared__ int s_refs[kQuads * kStackDepth4];
+    __shared__ float s_keys[kQuads * kStackDepth4];
+    const int lane = threadIdx.x, c = lane & 3, base = lane & ~3;
+    int* refs = s_refs + (lane >> 2);  // entries kQuads apart
+    float* keys = s_keys + (lane >> 2);
+    const int64_t n = a.n_grid, id = (int64_t)blockIdx.x * kQuads + (lane >> 2);
+    if (blockIdx.x == 0 && lane == 0) *a.count = 0;
+    if (id >= n * n * n) return;
+    const D3 p = node_position(a, (int)(id % n), (int)(id / n % n), (int)(id / (n * n)));
+    const Around x = around(p.x), y = around(p.y), z = around(p.z);
+    double best = __builtin_inf();  // of this lane's triangles
+    float bound = __builtin_inff();  // of all four lanes', from above
+    int sp = 0, ref = 0;
+    for (;;) {
+        bool found = false;
+        if (ref >= 0) {
+            const float* q = reinterpret_cast<const float*>(a.nodes4 + 8 * (int64_t)ref) + c;
+            const float b = box_below(x, y, z, q[0], q[4], q[8], q[12], q[16], q[20]);
+            const int child = bits_i(q[24]);
+            const bool hit = b <= bound && child != kEmptyRef;
+            const int hits = (int)(__ballot(hit) >> base) & 15;
+            // place among the children to visit, nearest first (equal ones in slot order)
+            int place = 0;
+            for (int o = 1; o < 4; ++o) {
+                const float other = __shfl_xor(b, o, kWave);
+                if ((hits >> (c ^ o) & 1) && (other < b || (other == b && (c ^ o) < c))) ++place;
+            }
+            const int behind = __popc(hits) - 1;
+            if (hit && place > 0) {
+                refs[(sp + behind - place) * kQuads] = child;
+                keys[(sp + behind - place) * kQuads] = b;
+            }
+            if (behind >= 0) {
+                const int first = (int)(__ballot(hit && place == 0) >> base) & 15;
+                ref = __shfl(child, base + __ffs(first) - 1, kWave);
+                sp += behind;
+                found = true;
+            }
+        } else {
+            const int first = (~ref) >> 3, count = (~ref) & 7;
+            for (int t = c; t < count; t += 4) {
+                const float4* tp = a.tris + 3 * (int64_t)(first + t);
+                const float4 v0 = tp[0], v1 = tp[1], v2 = tp[2];
+                const float b = triangle_below(x, y, z, v0, v1, v2);
+                if (b <= bound) best = fmin(best, tri_dist2(p, dvert(v0), dvert(v1), dvert(v2)));
+            }
+            bound = quad_min(bound_of(best));
+        }
+        // the four lanes read what each other wrote
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        while (!found && sp > 0) {
+            --sp;
+            ref = refs[sp * kQuads];
+            found = keys[sp * kQuads] <= bound;
+        }
+        if (!found) break;
+    }
+    best = fmin(best, __shfl_xor(best, 1, kWave));
+    best = fmin(best, __shfl_xor(best, 2, kWave));
+    if (c == 0) a.out[id] = (float)sqrt(best);
 }
 
 // ---------------------------------------------------------------------------
@@ -312,7 +394,6 @@ __device__ D3 cast_direction() {
     return d3(0.61 / len, 0.5177 / len, 0.6003 / len);
 }
 
-constexpr int kCastRays = kWave / 4;  // rays of a wavefront
 constexpr int kCastBlocks = 8192;
 
 // Winding number of every listed node: signed crossings of its ray with the
@@ -323,14 +404,14 @@ constexpr int kCastBlocks = 8192;
 // this way, on four times the wavefronts (0.42 -> 0.15 ms at 128^3 against one
 // lane per ray).
 __global__ __launch_bounds__(kWave) void k_sdf_cast(SdfBuildArgs a) {
-    __shared__ int s_stack[kCastRays * kStackAll4];
+    __shared__ int s_stack[kQuads * kStackAll4];
     const int lane = threadIdx.x, c = lane & 3;
-    int* stack = s_stack + (lane >> 2);  // entries kCastRays apart
+    int* stack = s_stack + (lane >> 2);  // entries kQuads apart
     const int64_t n = a.n_grid;
     const D3 D = cast_direction();
     const float ix = (float)(1.0 / D.x), iy = (float)(1.0 / D.y), iz = (float)(1.0 / D.z);
     const uint32_t total = *a.count;
-    for (uint32_t at = blockIdx.x * kCastRays + (lane >> 2); at < total; at += gridDim.x * kCastRays) {
+    for (uint32_t at = blockIdx.x * kQuads + (lane >> 2); at < total; at += gridDim.x * kQuads) {
         const uint32_t id = a.list[at];
         const D3 p = node_position(a, (int)(id % n), (int)(id / n % n), (int)(id / (n * n)));
         const Around x = around(p.x), y = around(p.y), z = around(p.z);
@@ -345,7 +426,7 @@ __global__ __launch_bounds__(kWave) void k_sdf_cast(SdfBuildArgs a) {
                 const float out = fminf(fminf((hx - x.lo) * ix, (hy - y.lo) * iy), (hz - z.lo) * iz);
                 const bool hit = in <= out * (1.0f + 2e-6f) && child != kEmptyRef;
                 const int hits = (int)(__ballot(hit) >> (lane & ~3)) & 15;
-                if (hit) stack[(sp + __popc(hits & ((1 << c) - 1))) * kCastRays] = child;
+                if (hit) stack[(sp + __popc(hits & ((1 << c) - 1))) * kQuads] = child;
                 sp += __popc(hits);
             } else {
                 const int first = (~ref) >> 3, count = (~ref) & 7;
@@ -357,7 +438,7 @@ __global__ __launch_bounds__(kWave) void k_sdf_cast(SdfBuildArgs a) {
             if (sp == 0) break;
             // the four lanes read what one of them wrote
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            ref = stack[--sp * kCastRays];
+            ref = stack[--sp * kQuads];
         }
         wind += __shfl_xor(wind, 1, kWave);
         wind += __shfl_xor(wind, 2, kWave);
@@ -390,6 +471,22 @@ hipError_t launch_mesh_boundary(const float4* tris, int64_t n_tris, unsigned lon
     return hipGetLastError();
 }
 
+// Whether the nodes of a grid lie too far apart beside the triangles for a wavefront to
+// search for 64 of them at once.  `spacing` is a voxel in triangles of a surface that
+// spans the mesh once.  A packet visits what any of its nodes needs, one after the
+// other; four lanes to a node visit what that node needs, on four times the wavefronts,
+// and share none of it.  Packets against lanes of their own, the whole field in us:
+// 188,572 triangles at 16^3 (spacing 39) 4,380 and 340, 32^3 (16) 1,550 and 505, 48^3
+// (10) 1,230 and 720, 64^3 (7) 1,090 and 1,170, 128^3 (3.5) 1,600 and 5,700; on a grid
+// four times the mesh 64^3 (27) 2,800 and 630, 128^3 (13) 1,850 and 3,500; 25,740 on
+// that grid at 64^3 (9.9) 1,080 and 550.  Up to 40^3 packets leave SIMDs without a
+// wavefront: 1,324 triangles at 32^3 (1.3) 215 and 191, 44^3 (0.9) 224 and 221, 64^3
+// (0.6) 240 and 450.
+static bool nodes_apart(const SdfBuildArgs& a) {
+    const float spacing = a.h * sqrtf((float)a.n_tris) / a.extent;
+    return a.n_grid <= 512 && spacing > (a.n_grid <= 40 ? 1.0f : 0.15f * (float)a.n_grid);
+}
+
 hipError_t launch_sdf_build(const SdfBuildArgs& args, void* scratch, size_t scratch_bytes, hipStream_t stream) {
     const size_t n = (size_t)args.n_grid, total = n * n * n;
     if (n < 2 || n > 1024 || !scratch || scratch_bytes < sdf_build_scratch(args.n_grid)) return hipErrorInvalidValue;
@@ -398,7 +495,11 @@ hipError_t launch_sdf_build(const SdfBuildArgs& args, void* scratch, size_t scra
     a.list = a.count + 4;
     a.label = reinterpret_cast<uint16_t*>(a.list + total);
     const unsigned nt = (unsigned)(n + 3) / 4, tiles = (unsigned)(n + kTile - 1) / kTile;
-    hipLaunchKernelGGL(k_sdf_nearest, dim3(nt * nt * nt), dim3(kWave), 0, stream, a, a.nodes4, a.tris, a.out);
+    if (nodes_apart(a))
+        hipLaunchKernelGGL(k_sdf_nearest_apart, dim3((unsigned)((total + kQuads - 1) / kQuads)), dim3(kWave), 0, stream,
+                           a);
+    else
+        hipLaunchKernelGGL(k_sdf_nearest, dim3(nt * nt * nt), dim3(kWave), 0, stream, a, a.nodes4, a.tris, a.out);
     hipLaunchKernelGGL(k_sdf_components, dim3(tiles * tiles * tiles), dim3(kTileNodes), 0, stream, a);
     hipLaunchKernelGGL(k_sdf_cast, dim3(kCastBlocks), dim3(kWave), 0, stream, a);
     hipLaunchKernelGGL(k_sdf_sign, dim3((unsigned)((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, a);

@@ -31,3 +31,25 @@ def test_squares_below_the_normal_range(scale, count, n):
     verts, tris = loose(count, 0.4, 5)
     g4 = np.array([-0.1, -0.1, -0.1, 1.2 / (n - 1)], np.float32) * np.float32(scale)
     check(verts * np.float32(scale), tris, n, g4)
+
+
+@pytest.mark.parametrize("n, line", [(8, 1.0), (9, 1.0), (27, 1.0), (40, 1.0), (41, 6.15), (50, 7.5)])
+@pytest.mark.parametrize("side", [0.98, 1.02])
+@pytest.mark.parametrize("mesh", ["closed", "loose"])
+def test_both_searches(n, line, side, mesh):
+    """Grids on both sides of the line between packets of nodes and nodes by themselves (a
+    voxel in triangles of a surface that spans the mesh), with wavefronts not filled."""
+    from paper_2305_07253_amd import workloads as W
+    scene = W.make_scene(4, 6, 0.05, 0.2, box_subdiv=1, ico_splits=1)
+    verts, tris = (scene.verts, scene.tris) if mesh == "closed" else loose(150, 0.3, 9)
+    lo, extent = verts.min(0), float((verts.max(0) - verts.min(0)).max())
+    h = side * line * extent / len(tris) ** 0.5
+    g4 = np.append(lo + (0.37 * extent - 0.5 * h * (n - 1)), h).astype(np.float32)
+    check(verts, tris, n, g4, exterior=n % 2 == 0)
+
+
+def test_detailed_mesh_on_coarse_grid():
+    """Long searches: deep stacks, many boxes and triangles for each node."""
+    from paper_2305_07253_amd import workloads as W
+    scene = W.make_scene(5, 60, 0.01, 0.12, box_subdiv=4, ico_splits=2)
+    check(scene.verts, scene.tris, 17, W.room_grid(17))
