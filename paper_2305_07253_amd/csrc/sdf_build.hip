@@ -8,6 +8,7 @@
 //   k_sdf_components  nodes joined across surface-free balls, per 8^3 nodes
 //   k_sdf_cast        the winding number of one node per component
 //   k_sdf_sign        every other node takes its component's sign
+//   k_sdf_few         all of it for meshes of a few triangles
 #include "kernels.hpp"
 #include "sdf_device.hpp"
 
@@ -459,6 +460,27 @@ __global__ __launch_bounds__(kThreads) void k_sdf_sign(SdfBuildArgs a) {
     if (__builtin_bit_cast(uint32_t, a.out[at]) >> 31) a.out[id] = -a.out[id];
 }
 
+// Few triangles: every node goes through all of them and counts its own ray's crossings,
+// in one pass.  The passes for larger meshes cost launches and n^3 labels whatever the
+// mesh: 2 triangles at 128^3 229 us with them, 127 in this one (155 by one thread per node
+// and a tree), 30 at 128^3 326 and 304, at 256^3 2,036 and 1,820, 40 there 1,981 and 2,165.
+__global__ __launch_bounds__(kThreads) void k_sdf_few(SdfBuildArgs a) {
+    const int64_t n = a.n_grid, id = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (id >= n * n * n) return;
+    const D3 p = node_position(a, (int)(id % n), (int)(id / n % n), (int)(id / (n * n))), D = cast_direction();
+    const Around x = around(p.x), y = around(p.y), z = around(p.z);
+    double best = __builtin_inf();
+    int wind = a.exterior_solid ? 1 : 0;
+    for (int t = 0; t < (int)a.n_tris; ++t) {
+        const float4 v0 = a.tris[3 * t], v1 = a.tris[3 * t + 1], v2 = a.tris[3 * t + 2];
+        if (triangle_below(x, y, z, v0, v1, v2) <= bound_of(best))
+            best = fmin(best, tri_dist2(p, dvert(v0), dvert(v1), dvert(v2)));
+        wind += crossing(p, D, dvert(v0), dvert(v1), dvert(v2));
+    }
+    const float dist = (float)sqrt(best);
+    a.out[id] = wind >= 1 ? -dist : dist;
+}
+
 }  // namespace
 
 size_t sdf_build_scratch(int32_t n) { return 16 + (sizeof(uint32_t) + sizeof(uint16_t)) * (size_t)n * n * n; }
@@ -470,6 +492,8 @@ hipError_t launch_mesh_boundary(const float4* tris, int64_t n_tris, unsigned lon
                        tris, n_tris, sum);
     return hipGetLastError();
 }
+
+constexpr int64_t kFewTriangles = 32;  // k_sdf_few
 
 // Whether the nodes of a grid lie too far apart beside the triangles for a wavefront to
 // search for 64 of them at once.  `spacing` is a voxel in triangles of a surface that
@@ -495,6 +519,10 @@ hipError_t launch_sdf_build(const SdfBuildArgs& args, void* scratch, size_t scra
     a.list = a.count + 4;
     a.label = reinterpret_cast<uint16_t*>(a.list + total);
     const unsigned nt = (unsigned)(n + 3) / 4, tiles = (unsigned)(n + kTile - 1) / kTile;
+    if (a.n_tris <= kFewTriangles) {
+        hipLaunchKernelGGL(k_sdf_few, dim3((unsigned)((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, a);
+        return hipGetLastError();
+    }
     if (nodes_apart(a))
         hipLaunchKernelGGL(k_sdf_nearest_apart, dim3((unsigned)((total + kQuads - 1) / kQuads)), dim3(kWave), 0, stream,
                            a);

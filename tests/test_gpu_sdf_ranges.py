@@ -53,3 +53,28 @@ def test_detailed_mesh_on_coarse_grid():
     from paper_2305_07253_amd import workloads as W
     scene = W.make_scene(5, 60, 0.01, 0.12, box_subdiv=4, ico_splits=2)
     check(scene.verts, scene.tris, 17, W.room_grid(17))
+
+
+@pytest.mark.parametrize("n", [8, 13, 33])
+@pytest.mark.parametrize("count", [0, 1, 2, 31, 32, 33])
+def test_few_triangles(count, n):
+    """Around the count up to which one pass goes through all triangles for every node."""
+    verts, tris = loose(count, 0.4, count)
+    g4 = np.array([-0.2, -0.1, -0.15, 1.3 / (n - 1)], np.float32)
+    if count == 0:
+        import paper_2305_07253_amd as hyb
+        with pytest.raises(hyb.HybError):  # every sample is infinite
+            hyb.build_sdf(hyb.build_bvh(verts, tris), n, g4)
+        return
+    for exterior in (True, False):
+        check(verts, tris, n, g4, exterior)
+
+
+def test_walls_alone():
+    """A closed mesh of few triangles: solid outside, or inside once it is turned."""
+    from paper_2305_07253_amd import workloads as W
+    scene = W.make_scene(1, 1, 0.2, 0.3, box_subdiv=1, ico_splits=1)
+    walls = scene.tris[:12]
+    for tris in (walls, np.ascontiguousarray(walls[:, ::-1])):
+        for exterior in (True, False):
+            check(scene.verts, tris, 19, W.room_grid(19), exterior)
