@@ -51,14 +51,16 @@ constexpr int kSparse = 32;             // distinct blocks above which it sums n
 constexpr int kSumBlock = 512;
 constexpr int kSlotBits = 13;
 constexpr int kSlots = 1 << kSlotBits;  // of a workgroup's hash table
+constexpr int kGroupBits = 4;           // nodes in a row that the table keeps together
+constexpr int kGroup = 1 << kGroupBits;
 static_assert(kSlots >= 2 * 8 * kSumBlock, "at least half of the table stays empty");
 constexpr uint32_t kEmpty = 0xffffffffu;
 
-// Rays up to which no sort pays: its passes take 50 us and more whatever the count,
-// the unsorted rays' additional global adds take time per ray.  Unsorted against
-// sorted by block: 16k rays on 32^3 12 against 36 us, 128k on 64^3 48 against 85,
-// 256k on 128^3 76 against 101 (32^3 67 against 62, a narrow view 32 against 97), 900k
-// on 160^3 263 against 150, 1M on 128^3 301 against 163.
+// Rays up to which no sort pays, whatever their order: its passes take 40 us and more
+// whatever the count, the unsorted rays' additional global adds take time per ray.
+// Unsorted against sorted by block: 128k rays of an image on 128^3 13 us and 80, random
+// ones 43 and 90; 256k 22 and 90, 80 and 102 (on 32^3 62 and 66); 400k random rays 123
+// and 119, 1M 279 and 222.
 constexpr int64_t kUnsorted = 1 << 18;
 
 __host__ __device__ inline int blocks_per_axis(int n) { return (n - 1 + kCells - 1) / kCells; }
@@ -169,11 +171,18 @@ __global__ __launch_bounds__(kBwdBlock) void k_bwd_blocks(TraceArgs a, const flo
 }
 
 // Up to kUnsorted rays: one launch over the rays in the caller's order, each
-// workgroup's 512 rays summed by node in a hash table in LDS (linear probing; at most
-// 8 * 512 of its 8,192 slots are taken, so that every probe ends) before the nodes are
-// added.  Neighbouring rays of an image share nodes, and what narrow views or small
-// grids need is that few workgroups add at one node: 64k rays into about 20 cells take
-// 15 us so and 280 us when each wavefront sums its own.  64 KB: two workgroups per CU.
+// workgroup's 512 rays summed by node in a hash table in LDS before the nodes are added.
+// At most 8 * 512 of its 8,192 slots are taken, and the probes' odd stride meets every
+// slot, so that every probe ends.  Neighbouring rays of an image share nodes, and what
+// narrow views or small grids need is that few workgroups add at one node: 64k rays into
+// about 20 cells take 15 us so and 280 us when each wavefront sums its own.
+//
+// Bound by the global adds.  Sixteen nodes in a row along x keep their order in the table
+// (a probe that goes on leaves the group), so that a wavefront adds to few lines at once
+// where the rays hit a surface here and there: 256k random rays on 32^3 62 us instead of
+// 186 with every node hashed by itself, on 128^3 80 instead of 128; those of an image 23
+// instead of 33 and 22 instead of 39 (groups of 8 and 32 the same within 10%).  64 KB:
+// two workgroups per CU.
 __global__ __launch_bounds__(kSumBlock) void k_bwd_sum(TraceArgs a, const float* __restrict__ t_hit,
                                                        const float* __restrict__ grad_t,
                                                        float* __restrict__ grad_grid) {
@@ -193,12 +202,13 @@ __global__ __launch_bounds__(kSumBlock) void k_bwd_sum(TraceArgs a, const float*
         uint32_t node[8], slot[8], old[8];
         for (int c = 0; c < 8; ++c) {
             node[c] = (uint32_t)cell + (c & 1) + n * (((c >> 1) & 1) + n * (c >> 2));
-            slot[c] = (node[c] * 2654435769u) >> (32 - kSlotBits);
+            slot[c] = (((node[c] >> kGroupBits) * 2654435769u) >> (32 - kSlotBits + kGroupBits) << kGroupBits) +
+                      (node[c] & (kGroup - 1));
             old[c] = atomicCAS(&s_node[slot[c]], kEmpty, node[c]);
         }
         for (int c = 0; c < 8; ++c) {
             while (old[c] != kEmpty && old[c] != node[c]) {
-                slot[c] = (slot[c] + 1) % kSlots;
+                slot[c] = (slot[c] + kGroup + 1) % kSlots;
                 old[c] = atomicCAS(&s_node[slot[c]], kEmpty, node[c]);
             }
             atomicAdd(&s_sum[slot[c]], v[c]);
