@@ -249,7 +249,7 @@ hyb_status hyb_trace(hyb_bvh bvh, hyb_sdf sdf, const hyb_rays* rays, int64_t n, 
     // is the distance-field query on [tmin, tmax]: its own kernel runs it, the
     // same per-ray arithmetic without the traversal code or the LDS stack.
     const int mode = threshold == 0.0f ? hyb::kDfOnly : hyb::kCombined;
-    return from_hip(hyb::launch_trace(mode, false, a, static_cast<hipStream_t>(stream)));
+    return from_hip(hyb::launch_trace(mode, false, a, bvh->n_tris, static_cast<hipStream_t>(stream)));
 }
 
 hyb_status hyb_trace_bvh(hyb_bvh bvh, const hyb_rays* rays, int64_t n, float tmax, hyb_hits* hits, void* stream) {
@@ -260,7 +260,7 @@ hyb_status hyb_trace_bvh(hyb_bvh bvh, const hyb_rays* rays, int64_t n, float tma
     hyb::TraceArgs a;
     fill_trace_args(a, rays, hits, n, tmax, __builtin_inff());
     fill_scene(a, bvh, nullptr);
-    return from_hip(hyb::launch_trace(hyb::kBvhOnly, false, a, static_cast<hipStream_t>(stream)));
+    return from_hip(hyb::launch_trace(hyb::kBvhOnly, false, a, bvh->n_tris, static_cast<hipStream_t>(stream)));
 }
 
 hyb_status hyb_trace_df(hyb_sdf sdf, const hyb_rays* rays, int64_t n, float tmax, hyb_hits* hits, void* stream) {
@@ -271,7 +271,7 @@ hyb_status hyb_trace_df(hyb_sdf sdf, const hyb_rays* rays, int64_t n, float tmax
     hyb::TraceArgs a;
     fill_trace_args(a, rays, hits, n, tmax, 0.0f);
     fill_scene(a, nullptr, sdf);
-    return from_hip(hyb::launch_trace(hyb::kDfOnly, false, a, static_cast<hipStream_t>(stream)));
+    return from_hip(hyb::launch_trace(hyb::kDfOnly, false, a, 0, static_cast<hipStream_t>(stream)));
 }
 
 hyb_status hyb_trace_shadow(hyb_bvh bvh, hyb_sdf sdf, const hyb_rays* rays, int64_t n, float tmax,
@@ -285,7 +285,7 @@ hyb_status hyb_trace_shadow(hyb_bvh bvh, hyb_sdf sdf, const hyb_rays* rays, int6
     hyb::TraceArgs a;
     fill_trace_args(a, rays, hits, n, tmax, threshold_start, threshold_end);
     fill_scene(a, bvh, sdf);
-    return from_hip(hyb::launch_trace(hyb::kShadow, false, a, static_cast<hipStream_t>(stream)));
+    return from_hip(hyb::launch_trace(hyb::kShadow, false, a, bvh->n_tris, static_cast<hipStream_t>(stream)));
 }
 
 hyb_status hyb_df_backward(hyb_sdf sdf, const hyb_rays* rays, int64_t n, float tmax, const float* t_hit,
@@ -332,7 +332,7 @@ hyb_status hyb_trace_counters(hyb_bvh bvh, hyb_sdf sdf, const hyb_rays* rays, in
                     mode == 3 ? threshold : 0.0f);
     fill_scene(a, mode == 2 ? nullptr : bvh, mode == 1 ? nullptr : sdf);
     a.counts = counts;
-    return from_hip(hyb::launch_trace(mode, true, a, static_cast<hipStream_t>(stream)));
+    return from_hip(hyb::launch_trace(mode, true, a, 0, static_cast<hipStream_t>(stream)));
 }
 
 }  // extern "C"

@@ -462,12 +462,13 @@ hyb_status tune_item_threshold(hyb_batch_s* b, int32_t item, const std::vector<f
     ref.u = reinterpret_cast<float*>(ref.prim + n);
     ref.v = ref.u + n;
     ref.tau = __builtin_inff();
-    HYB_TRY(hyb::launch_trace(hyb::kBvhOnly, false, ref, stream));
+    // as trees of no size: the traversal that the batch's kernel has
+    HYB_TRY(hyb::launch_trace(hyb::kBvhOnly, false, ref, 0, stream));
     float best_tau = __builtin_inff(), best_ms = std::numeric_limits<float>::infinity(), best_err = 0.0f;
     for (float c : cands) {
         a.tau = c;
         float ms = 0.0f;
-        hyb_status rc = time_min([&] { return hyb::launch_trace(hyb::kCombined, false, a, stream); }, reps, stream,
+        hyb_status rc = time_min([&] { return hyb::launch_trace(hyb::kCombined, false, a, 0, stream); }, reps, stream,
                                  e0, e1, &ms);
         if (rc != HYB_OK) return rc;
         HYB_TRY(hipMemsetAsync(d_count, 0, sizeof(unsigned long long), stream));

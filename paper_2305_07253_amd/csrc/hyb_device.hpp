@@ -1169,9 +1169,9 @@ HYB_HD Grid grid_of(const TraceArgs& a) {
 HYB_HD bool df_unusable(const TraceArgs& a) { return a.bounds && a.bounds[kBBad] != 0.0f; }
 
 // Which traversal a query's triangle segments take: known where the kernel is
-// chosen (kShortSegments, kLongSegments), or per ray (kAnySegments: the batch,
-// whose scenes differ).
-enum Segments : int { kAnySegments = 0, kShortSegments = 1, kLongSegments = 2 };
+// chosen (launch in trace.hip), or per ray (kAnySegments: the batch, whose scenes
+// differ).  kSmallTree: bvh_closest on long segments.
+enum Segments : int { kAnySegments = 0, kShortSegments = 1, kLongSegments = 2, kSmallTree = 3 };
 
 template <int SEG, bool COUNT, bool ANY, int LDS, bool PLANES = true>
 HYB_HD Hit bvh_segment(const TraceArgs& a, float ox, float oy, float oz, float dx, float dy, float dz,
@@ -1182,7 +1182,8 @@ HYB_HD Hit bvh_segment(const TraceArgs& a, float ox, float oy, float oz, float d
                                                  cnt, start);
     else
         return bvh_closest<COUNT, ANY, LDS, PLANES>(a.nodes, a.tris, ox, oy, oz, dx, dy, dz, inv, t0, t1, stack,
-                                                    stride, cnt, start, SEG == kAnySegments && sort);
+                                                    stride, cnt, start,
+                                                    SEG == kSmallTree || (SEG == kAnySegments && sort));
 }
 
 // One ray of a query (the body of the trace kernels).
@@ -1204,8 +1205,8 @@ HYB_HD void trace_ray(const TraceArgs& a, int64_t i, int* stack, int stride) {
             hit.t = __builtin_nanf("");
             hit.prim = -2;
         } else if (MODE == kBvhOnly) {
-            hit = bvh_segment<kLongSegments, COUNT, false, LDS>(a, ox, oy, oz, dx, dy, dz, ray_inv(dx, dy, dz), tmin,
-                                                                tmax, stack, stride, cnt, true);
+            hit = bvh_segment<SEG == kSmallTree ? kSmallTree : kLongSegments, COUNT, false, LDS>(
+                a, ox, oy, oz, dx, dy, dz, ray_inv(dx, dy, dz), tmin, tmax, stack, stride, cnt, true);
         } else if (MODE == kDfOnly) {
             const float t = df_first_root<FMT, COUNT>(g, ox, oy, oz, dx, dy, dz, ray_inv(dx, dy, dz), tmin, tmax, cnt);
             if (t != __builtin_inff()) {  // NaN: see df_first_root

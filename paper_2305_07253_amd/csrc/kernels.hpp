@@ -43,7 +43,8 @@ struct TraceArgs {
 
 // Rays of a wavefront (2^shift) of a launch over n rays.
 uint32_t rays_shift(int mode, int64_t n);
-hipError_t launch_trace(int mode, bool counters, const TraceArgs& a, hipStream_t stream);
+// n_tris: triangles of the tree (it picks the traversal, not the result).
+hipError_t launch_trace(int mode, bool counters, const TraceArgs& a, int64_t n_tris, hipStream_t stream);
 
 // Persistent multi-scene trace (combined query of every scene).  Work item w
 // covers rays [(w - item_start[s]) * rays_per_item, ...) of the scene s with

@@ -62,43 +62,58 @@ static hipError_t launch_segments(const TraceArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// Trees whose long segments bvh_closest searches at least as fast as bvh_closest_long:
+// voted steps save lane use where many wavefronts' rays part ways, and cost a lane that
+// goes its own way its turns, which is what a launch lasts in a small tree.
+//   closest hit, 2^19 rays or fewer: 1,052 triangles, an image's rays scattered a little,
+//   at 320x176 37 against 50 us and at 640x360 44 against 64, diffuse rays at 640x360 66
+//   against 78, at 960x544 106 against 102, at 1920x1080 300 against 285; 2,772 triangles,
+//   diffuse rays at 640x360 92 against 82
+//   any hit: 1,052 triangles at 480x272 25 against 29 and 36 against 45, at 1920x1080 160
+//   against 186; 4,884 triangles at 480x272 51 against 69, diffuse rays 146 against 137;
+//   25,740 triangles at 480x272 62 against 67, diffuse rays 162 against 142
+template <int MODE>
+static bool small_tree(int64_t n_tris, int64_t n) {
+    if constexpr (MODE == kShadow) return n_tris <= 8192;
+    return n_tris == 0 || (n_tris <= 2048 && n <= (int64_t(1) << 19));
+}
+
 // Triangle segments of at most kShortSegment voxels take the traversal for short
-// ones, all others (triangles only among them) the one for long ones.
+// ones, all others (triangles only among them) the one for long ones or small trees.
 template <int MODE, int FMT, bool COUNT>
-static hipError_t launch(const TraceArgs& a, hipStream_t stream) {
-    if constexpr (MODE == kCombined || MODE == kShadow) {
+static hipError_t launch(const TraceArgs& a, int64_t n_tris, hipStream_t stream) {
+    if constexpr (MODE == kCombined || MODE == kShadow)
         if (short_segments(a)) return launch_segments<MODE, FMT, COUNT, kShortSegments>(a, stream);
-        return launch_segments<MODE, FMT, COUNT, kLongSegments>(a, stream);
-    } else {
-        return launch_segments<MODE, FMT, COUNT, kLongSegments>(a, stream);
-    }
+    if constexpr (MODE != kDfOnly && !COUNT)
+        if (small_tree<MODE>(n_tris, a.n)) return launch_segments<MODE, FMT, COUNT, kSmallTree>(a, stream);
+    return launch_segments<MODE, FMT, COUNT, kLongSegments>(a, stream);
 }
 
 template <int MODE, bool COUNT>
-static hipError_t launch_fmt(const TraceArgs& a, hipStream_t stream) {
-    if constexpr (MODE == kBvhOnly) return launch<MODE, kF32, COUNT>(a, stream);
+static hipError_t launch_fmt(const TraceArgs& a, int64_t n_tris, hipStream_t stream) {
+    if constexpr (MODE == kBvhOnly) return launch<MODE, kF32, COUNT>(a, n_tris, stream);
     switch (a.fmt) {
-        case kF32: return launch<MODE, kF32, COUNT>(a, stream);
-        case kF16: return launch<MODE, kF16, COUNT>(a, stream);
-        case kF16B2: return launch<MODE, kF16B2, COUNT>(a, stream);
-        case kI8: return launch<MODE, kI8, COUNT>(a, stream);
+        case kF32: return launch<MODE, kF32, COUNT>(a, n_tris, stream);
+        case kF16: return launch<MODE, kF16, COUNT>(a, n_tris, stream);
+        case kF16B2: return launch<MODE, kF16B2, COUNT>(a, n_tris, stream);
+        case kI8: return launch<MODE, kI8, COUNT>(a, n_tris, stream);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_trace(int mode, bool counters, const TraceArgs& args, hipStream_t stream) {
+hipError_t launch_trace(int mode, bool counters, const TraceArgs& args, int64_t n_tris, hipStream_t stream) {
     if (args.n <= 0) return hipSuccess;
     TraceArgs a = args;
     if (a.xcd_run == 0) a.xcd_run = kXcdRun;  // xcd_block needs a run of at least 1
     switch (mode * 2 + (counters ? 1 : 0)) {
-        case 0: return launch_fmt<kCombined, false>(a, stream);
-        case 1: return launch_fmt<kCombined, true>(a, stream);
-        case 2: return launch_fmt<kBvhOnly, false>(a, stream);
-        case 3: return launch_fmt<kBvhOnly, true>(a, stream);
-        case 4: return launch_fmt<kDfOnly, false>(a, stream);
-        case 5: return launch_fmt<kDfOnly, true>(a, stream);
-        case 6: return launch_fmt<kShadow, false>(a, stream);
-        case 7: return launch_fmt<kShadow, true>(a, stream);
+        case 0: return launch_fmt<kCombined, false>(a, n_tris, stream);
+        case 1: return launch_fmt<kCombined, true>(a, n_tris, stream);
+        case 2: return launch_fmt<kBvhOnly, false>(a, n_tris, stream);
+        case 3: return launch_fmt<kBvhOnly, true>(a, n_tris, stream);
+        case 4: return launch_fmt<kDfOnly, false>(a, n_tris, stream);
+        case 5: return launch_fmt<kDfOnly, true>(a, n_tris, stream);
+        case 6: return launch_fmt<kShadow, false>(a, n_tris, stream);
+        case 7: return launch_fmt<kShadow, true>(a, n_tris, stream);
         default: return hipErrorInvalidValue;
     }
 }
