@@ -395,7 +395,9 @@ hyb_status hyb_batch_launch_eager(hyb_batch batch, void* stream);
  * +inf (exact) when none qualifies.
  * HYB_TUNE_LAUNCH: times the whole batch (fastest of `reps` eager launches) for
  * lds_depth {8,16,32} x rays_per_item {64,256,1024,4096} x blocks_per_cu
- * {1,2,4,8} and keeps the fastest.
+ * {1,2,4,8} and keeps the fastest.  A rays_per_item that cuts the batch into the
+ * same work items as a smaller one is left out (all but 64 for batches of up to
+ * 2^26 rays).
  * item_error (host, n_items floats, may be NULL) receives each item's error
  * rate at its chosen threshold (0 for items not tuned); best_ms (may be NULL)
  * the fastest whole-batch time of the final configuration.  Allocates 16 bytes

@@ -632,8 +632,14 @@ hyb_status hyb_batch_tune(hyb_batch batch, const hyb_batch_tune_opts* opts, floa
     if (rc == HYB_OK && (opts->flags & HYB_TUNE_LAUNCH)) {
         hyb_batch_config best = batch->cfg;
         float best_t = std::numeric_limits<float>::infinity();
+        uint64_t rays = 0;
+        for (const hyb::TraceArgs& a : batch->args) rays += static_cast<uint64_t>(a.n);
         for (int32_t lds : {8, 16, 32}) {
+            int32_t timed = 0;  // rays per work item of the candidates so far
             for (int32_t rpi : {64, 256, 1024, 4096}) {
+                const int32_t item = item_rays({lds, rpi, 1}, rays);
+                if (item == timed) continue;  // the same launches again
+                timed = item;
                 for (int32_t bpc : {1, 2, 4, 8}) {
                     if (rc != HYB_OK) break;
                     const hyb_batch_config c = {lds, rpi, bpc};
