@@ -92,10 +92,33 @@ inline hyb_status allocate_store(hyb_sdf_s* s, size_t* bytes) {
     return HYB_OK;
 }
 
+// Where the kernels read the caller's n^3 samples.  Device memory of this device is
+// read in place, if the allocation holds that many.  Other memory (of the host or
+// another device, which kernels may not be able to read) is copied into s->values first.
+inline hyb_status sample_source(hyb_sdf_s* s, const float*& in, hipStream_t stream) {
+    const size_t bytes = sizeof(float) * static_cast<size_t>(s->n) * s->n * s->n;
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, in) == hipSuccess && at.type == hipMemoryTypeDevice && at.device == s->device) {
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        HYB_TRY(hipMemGetAddressRange(&base, &size, const_cast<float*>(in)));
+        const size_t offset = static_cast<size_t>(reinterpret_cast<const char*>(in) - static_cast<const char*>(base));
+        return offset <= size && bytes <= size - offset ? HYB_OK : HYB_ERR_HIP;
+    }
+    (void)hipGetLastError();  // memory that HIP does not know is not an error here
+    HYB_TRY(hipMemcpyAsync(s->values, in, bytes, hipMemcpyDefault, stream));
+    in = s->values;
+    return HYB_OK;
+}
+
 // Stores the samples `in` (launch_store) with their step bounds.  Deferred, the
 // bounds stay on the device; else this waits for them, and a sample that is not
 // finite (or an F16 overflow) is an error.
 inline hyb_status store_samples(hyb_sdf_s* s, const float* in, bool deferred, hipStream_t stream) {
+    if (in != s->values) {
+        const hyb_status rc = sample_source(s, in, stream);
+        if (rc != HYB_OK) return rc;
+    }
     if (!s->blocks) HYB_TRY(hipMalloc(&s->blocks, sizeof(float) * hyb::kBoundValues * hyb::store_blocks(s->n)));
     if (!s->dev_bounds) HYB_TRY(hipMalloc(&s->dev_bounds, sizeof(float) * hyb::kDeviceBounds));
     HYB_TRY(hyb::launch_store(s->layout, in, s->n, s->grid4[3], s->values, s->store, s->scales, s->blocks, two_e_of(s),
