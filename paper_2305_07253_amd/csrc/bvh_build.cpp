@@ -299,7 +299,9 @@ int build_bvh_host(const float* verts, int64_t n_verts, const int32_t* tris, int
     // Flatten depth-first: internal nodes get consecutive output indices, leaves
     // become references into the leaf-ordered triangle array.
     out->nodes.clear();
-    out->tris.assign(static_cast<size_t>(12 * n_tris), 0.0f);
+    out->tris.clear();
+    out->tris.reserve(static_cast<size_t>(12 * n_tris + 4));  // the library appends four words
+    out->tris.resize(static_cast<size_t>(12 * n_tris), 0.0f);
     int64_t tri_cursor = 0;
     auto leaf_ref = [&](const TmpNode& n) -> int32_t {
         int32_t first = static_cast<int32_t>(tri_cursor);

@@ -1,7 +1,8 @@
 // The stack of traversals of a four-wide tree, for the test: reads triangles (9 floats
 // each) from stdin; writes the build's status, its bound of a traversal that enters the
 // nearest child and pushes the others, the most entries of one that pushes every child
-// (found by walking the tree), and the entries that such a traversal has.
+// (found by walking the tree), the entries that such a traversal has, and whether the
+// four words that the library appends to the triangles have room.
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -32,7 +33,7 @@ int main() {
         for (int c = 0; c < kids; ++c)
             if (refs[c] >= 0) todo.push_back({refs[c], held + kids - 1});
     }
-    const int32_t out[4] = {rc, b.stack4, most, hyb::kStackAll4};
-    fwrite(out, 4, 4, stdout);
+    const int32_t out[5] = {rc, b.stack4, most, hyb::kStackAll4, b.tris.capacity() >= 12 * (size_t)n + 4};
+    fwrite(out, 4, 5, stdout);
     return 0;
 }

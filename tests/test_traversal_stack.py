@@ -40,7 +40,7 @@ def test_deepest_trees(stack):
     bounds, refused = set(), 0
     for levels in range(25, 33):
         for last in range(1, 10):
-            rc, bound, most, room = (int(x) for x in stack(clusters(levels, last)))
+            rc, bound, most, room = (int(x) for x in stack(clusters(levels, last))[:4])
             if rc == UNSUPPORTED:
                 refused += 1
                 continue
@@ -48,3 +48,10 @@ def test_deepest_trees(stack):
             assert most <= room
             bounds.add(bound)
     assert LIMIT in bounds and refused
+
+
+@pytest.mark.parametrize("count", [0, 1, 2, 1000])
+def test_triangles_stay_where_they_are(stack, count):
+    """What the library appends to a tree's triangles moves no megabytes."""
+    rc, *_, room = stack(np.random.default_rng(count).random((count, 3, 3)))
+    assert rc == 0 and room == 1
