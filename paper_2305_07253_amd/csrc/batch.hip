@@ -30,9 +30,11 @@ constexpr int kWave = 64;
 constexpr int kQueueStride = 8;
 
 // Bound by the latency of its wavefronts (four per SIMD in the default configuration)
-// and by the last of them.  Held to five wavefronts per SIMD: at six, 80 VGPRs, FP32 takes
-// 407 us for 12 scenes with 1.7M rays instead of 374 (at six blocks per CU 347 instead of
-// 342), at seven 508; left alone F16 takes 99 registers and loses the fifth.
+// and by the last of them.  Held to five wavefronts per SIMD (FP32 87 VGPRs, so no more than
+// five blocks per CU whatever the configuration asks for): held to six, 80 VGPRs, FP32
+// takes 407 us for 12 scenes with 1.7M rays instead of 374 at the default four blocks
+// per CU, and with as many blocks as fit, six against five, 347 instead of 342; at
+// seven 508; left alone F16 takes 99 registers and loses the fifth.
 //
 // Blocks share a counter with those of their die (the dispatcher hands block b to die
 // b mod kXcds): counters that eight dies add to serve a pop in 17 ns, which at items of
@@ -322,7 +324,8 @@ hyb_status persistent_grid(int fmt, const hyb_batch_config& cfg, int n_cu, uint6
     HYB_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, hyb::kBatchBlock, hyb::batch_lds_bytes(cfg.lds_depth)));
     const int64_t per_cu = std::max(1, std::min(occ, cfg.blocks_per_cu));
     // 4 wavefronts per block, as many blocks on each die's counter
-    const int64_t blocks_needed = (static_cast<int64_t>(work_items) + 4 * hyb::kXcds - 1) / (4 * hyb::kXcds) * hyb::kXcds;
+    const int64_t blocks_needed =
+        (static_cast<int64_t>(work_items) + 4 * hyb::kXcds - 1) / (4 * hyb::kXcds) * hyb::kXcds;
     *grid = dim3(static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(per_cu * n_cu, blocks_needed))));
     return HYB_OK;
 }

@@ -185,7 +185,8 @@ __global__ __launch_bounds__(kBwdBlock) void k_bwd_blocks(TraceArgs a, const flo
             acc[q] = 0.0f;
             const uint32_t block = s_block[base + q / kNodes];
             const int r = q % kNodes;
-            const int i = (int)(block % nb) * kCells + r % kSide, jj = (int)(block / nb % nb) * kCells + r / kSide % kSide,
+            const int i = (int)(block % nb) * kCells + r % kSide,
+                      jj = (int)(block / nb % nb) * kCells + r / kSide % kSide,
                       k = (int)(block / nb / nb) * kCells + r / (kSide * kSide);
             unsafeAtomicAdd(grad_grid + i + (int64_t)n * (jj + (int64_t)n * k), sum);
         }
@@ -299,7 +300,8 @@ hipError_t launch_df_backward(const TraceArgs& a, const float* t_hit, const floa
     e = rocprim::radix_sort_pairs<BwdSortConfig>(p + 4 * arr, temp_bytes, keys, rays, static_cast<int>(a.n), 0,
                                                  key_bits(a.n_grid), stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bwd_blocks, dim3(blocks), dim3(kBwdBlock), 0, stream, a, t_hit, grad_t, keys.current(), rays.current(), grad_grid, none);
+    hipLaunchKernelGGL(k_bwd_blocks, dim3(blocks), dim3(kBwdBlock), 0, stream, a, t_hit, grad_t, keys.current(),
+                       rays.current(), grad_grid, none);
     return hipGetLastError();
 }
 

@@ -135,7 +135,8 @@ __global__ __launch_bounds__(kThreads) void k_store(const float* in, int32_t n, 
                 v = dequantized<FMT>(f, i, j, k, nb, scales);
                 if (!finite(f) || !finite(v)) best[4] = 1.0f;
                 // a face shared with the next tile is that tile's to write
-                const bool mine = (x < kTileX || i == cells) && (y < kTileY || j == cells) && (z < kTileZ || k == cells);
+                const bool mine =
+                    (x < kTileX || i == cells) && (y < kTileY || j == cells) && (z < kTileZ || k == cells);
                 if (values && mine) values[id] = v;
             }
             node[q] = v;

@@ -125,9 +125,8 @@ __device__ void order_keys(uint32_t& ka, int& ra, uint32_t& kb, int& rb) {
 //
 // Bound by VALU issue, more than half of it the FP64 tests: at 128^3 on the
 // 188,572-triangle scene a wavefront visits 58 nodes and measures 62 triangles.
-// 1.18 ms there, 0.12 ms at 32^3 on 1,052 triangles.  One thread per node with
-// its own FP64 traversal and its stack in scratch took 6.26 ms and 0.24 ms, the
-// sign included.
+// 1.25 ms there.  One thread per node with its own FP64 traversal and its stack in
+// scratch took 6.26 ms, the sign included.
 __global__ __launch_bounds__(kWave) void k_sdf_nearest(SdfBuildArgs a, const float4* __restrict__ nodes4,
                                                        const float4* __restrict__ tris, float* __restrict__ out) {
     constexpr int kMiddle = 1 + 4 + 16;  // lane of node (1, 1, 1): at most 2 sqrt(3) h from any lane
@@ -520,7 +519,8 @@ hipError_t launch_sdf_build(const SdfBuildArgs& args, void* scratch, size_t scra
     a.label = reinterpret_cast<uint16_t*>(a.list + total);
     const unsigned nt = (unsigned)(n + 3) / 4, tiles = (unsigned)(n + kTile - 1) / kTile;
     if (a.n_tris <= kFewTriangles) {
-        hipLaunchKernelGGL(k_sdf_few, dim3((unsigned)((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream, a);
+        hipLaunchKernelGGL(k_sdf_few, dim3((unsigned)((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, stream,
+                           a);
         return hipGetLastError();
     }
     if (nodes_apart(a))

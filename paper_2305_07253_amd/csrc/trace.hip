@@ -1,8 +1,8 @@
 // Trace kernels: the combined query and the two pure baselines.
 //
-// One ray per lane (in small launches, several lanes per ray).  Rays and hits are SoA arrays, so each of the seven input
-// and four output streams is read or written with fully coalesced 256-byte
-// wavefront accesses.  The BVH stack lives in LDS ([depth][thread] so the 64
+// One ray per lane (in small launches, several lanes per ray).  Rays and hits are SoA
+// arrays, so each of the seven input and four output streams is read or written with
+// fully coalesced 256-byte wavefront accesses.  The BVH stack lives in LDS ([depth][thread] so the 64
 // lanes of a wavefront hit 64 distinct banks), with a small private spill area
 // for the rare paths deeper than the LDS part.
 #include "hyb_device.hpp"
@@ -23,7 +23,10 @@ namespace hyb {
 // 85 and 118 -> 105 us, at 262,144 (64 rays each already) 32 rays would take 146
 // for 113 us.  The distance field alone diverges less: to 1,024 wavefronts and
 // 8,192 rays (1,000 rays 29 -> 25 us, 4,096 34 -> 27 us), 16,384 rays took 3 to
-// 5% longer.
+// 5% longer.  Launches that share the chip with others pay for their spread: four
+// streams of 1,000 rays each through the GI scene 27 -> 14 us a launch, of 16,384 28 to
+// 31 -> 31, of 65,536 random rays in the small room 14 -> 17 (half as many wavefronts
+// would take 14 there, and alone 50% longer at 4,000 rays).
 uint32_t rays_shift(int mode, int64_t n) {
     if (mode == kDfOnly && n > 8192) return 6;
     const int64_t waves = mode == kDfOnly ? 1024 : 2048;
